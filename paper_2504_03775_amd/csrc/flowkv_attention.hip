@@ -67,6 +67,10 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(1))) u32x4 gvec4;
 typedef __attribute__((address_space(1))) u32x2 gvec2;
+// float vectors of the workspace and the output, which are only 4-byte aligned
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 // Pass-1 workgroups: 8 waves on the vector units, 4 on the matrix cores.
@@ -96,8 +100,8 @@ struct AttnArgs {
   const int32_t* tables;                // (n_req, max_blocks)
   const int32_t* seq_lens;              // (n_req)
   float* out;                           // (n_req, Hq, Dh) f32
-  float* ws;                            // (n_req, Hq, max_splits, Dh + 2) f32
-  int32_t layer, num_layers, block_size, kv_heads, q_heads, max_blocks;
+  float* ws;                            // the splits' records (record_sums, record_ml)
+  int32_t layer, n_req, block_size, kv_heads, q_heads, max_blocks;
   int32_t split_tokens, max_splits, max_seq_len;
   float scale_log2;                     // scale * log2(e)
   // the requests' lengths, when the caller passed them on the host (the
@@ -116,6 +120,21 @@ __device__ __forceinline__ int clamp_len(const AttnArgs& a, int T) {
   return T < a.max_seq_len ? T : a.max_seq_len;
 }
 
+// The workspace holds a record per (request, query head, split): the weighted
+// V (Dh floats) of all records first, then all records' (reference max, sum).
+// (With a record's Dh + 2 floats together, no 16-byte access to a weighted V
+// was aligned but every second one.)
+__device__ __forceinline__ int64_t record_at(const AttnArgs& a, int r, int h, int split) {
+  return (int64_t(r) * a.q_heads + h) * a.max_splits + split;
+}
+__device__ __forceinline__ float* record_sums(const AttnArgs& a, int dh, int64_t rec) {
+  return a.ws + rec * dh;
+}
+__device__ __forceinline__ f32x2u* record_ml(const AttnArgs& a, int dh, int64_t rec) {
+  const int64_t n = int64_t(a.n_req) * a.q_heads * a.max_splits;
+  return reinterpret_cast<f32x2u*>(a.ws + n * dh) + rec;
+}
+
 // Without the lengths in the arguments, a split at or past its request's end
 // still leaves a record, an empty partial (max -inf, sum 0) for each of its
 // kG query heads, so that the merge reads every split up to max_splits
@@ -124,11 +143,7 @@ __device__ __forceinline__ int clamp_len(const AttnArgs& a, int T) {
 template <int kG, int kDh>
 __device__ __forceinline__ void write_empty_partial(const AttnArgs& a, int g, int split, int r,
                                                     int tid) {
-  if (tid < kG) {
-    float* e = a.ws + ((int64_t(r) * a.q_heads + g * kG + tid) * a.max_splits + split) * (kDh + 2);
-    e[0] = -INFINITY;
-    e[1] = 0.f;
-  }
+  if (tid < kG) *record_ml(a, kDh, record_at(a, r, g * kG + tid, split)) = f32x2u{-INFINITY, 0.f};
 }
 
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -414,8 +429,6 @@ __global__ __launch_bounds__(kVecThreads) void decode_attn_split(const AttnArgs 
     }
   }
   __syncthreads();
-  float* const dst0 = a.ws + ((int64_t(r) * a.q_heads + g * kG) * a.max_splits + split) * (kDh + 2);
-  const int64_t head_stride = int64_t(a.max_splits) * (kDh + 2);
   if (tid < kG) {  // thread = query head of the group: rows x with x % kHS == its share
     const int sh = tid / kGl, h = tid % kGl;
     float M = -INFINITY;
@@ -426,8 +439,7 @@ __global__ __launch_bounds__(kVecThreads) void decode_attn_split(const AttnArgs 
       s_w[x][h] = w;
       L = fmaf(s_l[x][h], w, L);
     }
-    dst0[tid * head_stride] = M;
-    dst0[tid * head_stride + 1] = L;
+    *record_ml(a, kDh, record_at(a, r, g * kG + tid, split)) = f32x2u{M, L};
   }
   __syncthreads();
   // weight each row's sums, add the rows of a wave that share heads (lane
@@ -450,7 +462,7 @@ __global__ __launch_bounds__(kVecThreads) void decode_attn_split(const AttnArgs 
     float A = 0.f;
 #pragma unroll
     for (int x = 0; x < kVecThreads / 64; ++x) A += s_acc[x][h][d];
-    dst0[h * head_stride + 2 + d] = A;
+    record_sums(a, kDh, record_at(a, r, g * kG + h, split))[d] = A;
   }
 }
 
@@ -480,7 +492,6 @@ __global__ __launch_bounds__(kVecThreads) void decode_attn_split(const AttnArgs 
 //     slower for it.
 // The waves' partial (max, sum, weighted V) merge through LDS at the end.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 template <int kCtrl>
 __device__ __forceinline__ float dpp_max(float x) { return fmaxf(x, dpp<kCtrl>(x)); }
@@ -746,8 +757,6 @@ __global__ __launch_bounds__(kMfmaThreads) void decode_attn_split_mfma(const Att
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       if (4 * q4 + j < kG) s_o[(wave * kG + 4 * q4 + j) * kDh + 16 * t + c16] = o[t][j];
-  float* const dst0 = a.ws + ((int64_t(r) * a.q_heads + g * kG) * a.max_splits + split) * (kDh + 2);
-  const int64_t head_stride = int64_t(a.max_splits) * (kDh + 2);
   if (tid < kG) {
     float M = -INFINITY;
     for (int w = 0; w < kWaves; ++w) M = fmaxf(M, s_m[w][tid]);
@@ -757,8 +766,7 @@ __global__ __launch_bounds__(kMfmaThreads) void decode_attn_split_mfma(const Att
       s_w[w][tid] = wt;
       L = fmaf(s_l[w][tid], wt, L);
     }
-    dst0[tid * head_stride] = M;
-    dst0[tid * head_stride + 1] = L;
+    *record_ml(a, kDh, record_at(a, r, g * kG + tid, split)) = f32x2u{M, L};
   }
   __syncthreads();
   for (int i = tid; i < kG * kDh; i += kMfmaThreads) {
@@ -766,84 +774,119 @@ __global__ __launch_bounds__(kMfmaThreads) void decode_attn_split_mfma(const Att
     float A = 0.f;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) A = fmaf(s_o[(w * kG + h) * kDh + d], s_w[w][h], A);
-    dst0[h * head_stride + 2 + d] = A;
+    record_sums(a, kDh, record_at(a, r, g * kG + h, split))[d] = A;
   }
 }
 
-// Pass 2: one workgroup per (query head, request).  Every split up to
-// max_splits has a record (pass 1 leaves an empty one past a request's end;
-// with kLens the merge reads only the request's own splits instead), so the
-// merge needs no chain of dependent loads: a thread set of Dh threads takes
-// every (256 / Dh)-th split, kMergeChunk splits' records loaded at once (all
-// of them in one round for up to 256 / Dh x kMergeChunk splits), folded into
-// a running (max, sum, weighted V) that is rescaled when its max rises; the
-// sets then meet in LDS.
+// Pass 2: the splits' records of one (query head, request), by one wave (up to
+// kMergeChunk records per lane group; a workgroup then takes four heads) or by
+// the four waves of a workgroup.  A group of Dh / 4 lanes takes a record, 4
+// dims a lane, kMergeChunk records at once with no branch on their values (a
+// split past the end re-reads split 0 and is masked), folded into a running
+// (max, sum, weighted V) that is rescaled when its max rises; the groups then
+// meet by lane exchanges, the waves in LDS.
+// What bounds it: a launch's floor (about 3 us here) and one round of loads
+// that come from HBM, since pass 1 wrote them on other XCDs.  The form before
+// it took a float a lane and 16 records a thread however few there were: 48
+// requests of up to 6 splits, 32 heads, 6.5 us against 3.9; 32 requests x 64
+// heads x 16 splits at head_dim 64, 8.0 against 4.5; one request of 51 splits
+// 4.6 against 4.0.
 constexpr int kMergeThreads = 256;
-constexpr int kMergeChunk = 16;
+constexpr int kMergeChunk = 4;
 
-template <int kDh, bool kLens>
+struct Running {
+  float m, l;
+  f32x4 v;
+};
+
+// Both parts' sums under the larger reference; a part that saw no token has
+// m = -inf and weighs nothing.
+__device__ __forceinline__ Running join(const Running& a, const Running& b) {
+  Running r;
+  r.m = fmaxf(a.m, b.m);
+  const float wa = a.m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(a.m - r.m);
+  const float wb = b.m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(b.m - r.m);
+  r.l = a.l * wa + b.l * wb;
+  r.v = a.v * wa + b.v * wb;
+  return r;
+}
+
+template <int kDh, bool kLens, int kWavesPer>
 __global__ __launch_bounds__(kMergeThreads) void decode_attn_merge(const AttnArgs a) {
-  constexpr int kParts = kMergeThreads / kDh;
-  const int h = blockIdx.x, r = blockIdx.y, tid = threadIdx.x;
-  const int d = tid % kDh, part = tid / kDh;
+  constexpr int kLanes = kDh / 4;                // lanes per record
+  constexpr int kParts = 64 * kWavesPer / kLanes;
+  const int r = blockIdx.y, ln = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int h = kWavesPer == 1 ? blockIdx.x * (kMergeThreads / 64) + wave : blockIdx.x;
+  if (h >= a.q_heads) return;                    // (whole waves, and no barrier follows)
+  const int tid = kWavesPer == 1 ? ln : threadIdx.x;
+  const int d = 4 * (tid % kLanes), part = tid / kLanes;
   // records per (request, head); with the lengths in the arguments only the
   // request's own splits hold one
   int ns = a.max_splits;
   if constexpr (kLens) ns = (clamp_len(a, a.lens[r]) + a.split_tokens - 1) / a.split_tokens;
-  float* o = a.out + (int64_t(r) * a.q_heads + h) * kDh;
-  const float* src = a.ws + (int64_t(r) * a.q_heads + h) * a.max_splits * (kDh + 2);
-  float m = -INFINITY, l = 0.f, acc = 0.f;
+  const int64_t rec0 = record_at(a, r, h, 0);
+  const float* sums = record_sums(a, kDh, rec0) + d;
+  const f32x2u* ml = record_ml(a, kDh, rec0);
+  Running x{-INFINITY, 0.f, f32x4{0.f, 0.f, 0.f, 0.f}};
   for (int x0 = part; x0 < ns; x0 += kParts * kMergeChunk) {
     // branch-free loads: a split past the end re-reads split 0 and is
     // masked; an empty record's weighted V (never written) is not used
-    float ms[kMergeChunk], ls[kMergeChunk], vs[kMergeChunk];
+    f32x2u m[kMergeChunk];
+    f32x4u v[kMergeChunk];
 #pragma unroll
     for (int j = 0; j < kMergeChunk; ++j) {
-      const int x = x0 + j * kParts;
-      const float* e = src + int64_t(x < ns ? x : 0) * (kDh + 2);
-      ms[j] = e[0];
-      ls[j] = e[1];
-      vs[j] = e[2 + d];
-      if (x >= ns) ms[j] = -INFINITY;
+      const int s = x0 + j * kParts < ns ? x0 + j * kParts : 0;
+      m[j] = ml[s];
+      v[j] = *reinterpret_cast<const f32x4u*>(sums + int64_t(s) * kDh);
     }
-    // no branch on the records' values, so every load above issues at once
-    float cm = m;
-#pragma unroll
-    for (int j = 0; j < kMergeChunk; ++j) cm = fmaxf(cm, ms[j]);
-    const float c = m == -INFINITY ? 0.f : exp2f(m - cm);  // 1 when the max holds
-    l *= c;
-    acc *= c;
+    float cm = x.m;
 #pragma unroll
     for (int j = 0; j < kMergeChunk; ++j) {
-      const bool live = ms[j] != -INFINITY;
-      const float w = live ? exp2f(ms[j] - cm) : 0.f;
-      l = live ? fmaf(ls[j], w, l) : l;
-      acc = live ? fmaf(vs[j], w, acc) : acc;
+      if (x0 + j * kParts >= ns) m[j][0] = -INFINITY;
+      cm = fmaxf(cm, m[j][0]);
     }
-    m = cm;
+    const float c = x.m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(x.m - cm);
+    x.l *= c;
+    x.v *= c;
+#pragma unroll
+    for (int j = 0; j < kMergeChunk; ++j) {
+      const bool live = m[j][0] != -INFINITY;
+      const float w = live ? __builtin_amdgcn_exp2f(m[j][0] - cm) : 0.f;
+      x.l = live ? fmaf(m[j][1], w, x.l) : x.l;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x.v[k] = live ? fmaf(v[j][k], w, x.v[k]) : x.v[k];
+    }
+    x.m = cm;
   }
-  __shared__ float s_m[kParts], s_l[kParts];
-  __shared__ float s_a[kParts][kDh];
-  if (d == 0) {
-    s_m[part] = m;
-    s_l[part] = l;
+#pragma unroll
+  for (int off = kLanes; off < 64; off *= 2) {
+    Running y;
+    y.m = __shfl_xor(x.m, off);
+    y.l = __shfl_xor(x.l, off);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) y.v[k] = __shfl_xor(x.v[k], off);
+    x = join(x, y);
   }
-  s_a[part][d] = acc;
-  __syncthreads();
+  if constexpr (kWavesPer > 1) {
+    __shared__ float s_ml[kWavesPer][2];
+    __shared__ f32x4 s_v[kWavesPer][kLanes];
+    if (ln < kLanes) s_v[wave][ln] = x.v;
+    if (ln == 0) {
+      s_ml[wave][0] = x.m;
+      s_ml[wave][1] = x.l;
+    }
+    __syncthreads();
+    if (threadIdx.x >= kLanes) return;
+    x = Running{s_ml[0][0], s_ml[0][1], s_v[0][ln]};
+#pragma unroll
+    for (int w = 1; w < kWavesPer; ++w) x = join(x, Running{s_ml[w][0], s_ml[w][1], s_v[w][ln]});
+  }
   if (part == 0) {
-    float M = -INFINITY;
+    f32x4u o;
 #pragma unroll
-    for (int p = 0; p < kParts; ++p) M = fmaxf(M, s_m[p]);
-    float L = 0.f, A = 0.f;
-#pragma unroll
-    for (int p = 0; p < kParts; ++p) {
-      if (s_m[p] != -INFINITY) {
-        const float w = exp2f(s_m[p] - M);
-        L = fmaf(s_l[p], w, L);
-        A = fmaf(s_a[p][d], w, A);
-      }
-    }
-    o[d] = L > 0.f ? A / L : 0.f;
+    for (int k = 0; k < 4; ++k) o[k] = x.l > 0.f ? x.v[k] / x.l : 0.f;
+    *reinterpret_cast<f32x4u*>(a.out + (int64_t(r) * a.q_heads + h) * kDh + d) = o;
   }
 }
 
@@ -875,12 +918,15 @@ SplitFn pick_split(int D, int G, bool lm, bool lens) {
   return lens ? pick_split_lens<true>(D, G, lm) : pick_split_lens<false>(D, G, lm);
 }
 
-const void* pick_merge(int D, bool lens) {
-  if (D == 64)
-    return lens ? reinterpret_cast<const void*>(decode_attn_merge<64, true>)
-                : reinterpret_cast<const void*>(decode_attn_merge<64, false>);
-  return lens ? reinterpret_cast<const void*>(decode_attn_merge<128, true>)
-              : reinterpret_cast<const void*>(decode_attn_merge<128, false>);
+template <int D, bool L>
+const void* pick_merge_waves(bool one) {
+  return one ? reinterpret_cast<const void*>(decode_attn_merge<D, L, 1>)
+             : reinterpret_cast<const void*>(decode_attn_merge<D, L, 4>);
+}
+
+const void* pick_merge(int D, bool lens, bool one) {
+  if (D == 64) return lens ? pick_merge_waves<64, true>(one) : pick_merge_waves<64, false>(one);
+  return lens ? pick_merge_waves<128, true>(one) : pick_merge_waves<128, false>(one);
 }
 
 int32_t auto_split(int32_t n_req, int32_t max_seq_len) {
@@ -1104,7 +1150,7 @@ int launch_attention(const flowkv_pool* pool, int32_t layer, const void* q_dev, 
   a.out = out_dev;
   a.ws = static_cast<float*>(workspace_dev);
   a.layer = layer;
-  a.num_layers = pool->num_layers;
+  a.n_req = n_req;
   a.block_size = int32_t(bs);
   a.kv_heads = kv_heads;
   a.q_heads = q_heads;
@@ -1126,7 +1172,11 @@ int launch_attention(const flowkv_pool* pool, int32_t layer, const void* q_dev, 
                         args, 0, st);
   }
   if (e == hipSuccess) {
-    e = hipLaunchKernel(pick_merge(head_dim, lens), dim3(unsigned(q_heads), unsigned(n_req)),
+    // one wave per (query head, request) where its lane groups hold every
+    // record at once, a workgroup's four waves above
+    const bool one = a.max_splits <= kMergeChunk * 64 * 4 / head_dim;
+    e = hipLaunchKernel(pick_merge(head_dim, lens, one),
+                        dim3(unsigned(one ? (q_heads + 3) / 4 : q_heads), unsigned(n_req)),
                         dim3(kMergeThreads), args, 0, st);
   }
   if (e == hipSuccess) e = hipGetLastError();
