@@ -1,12 +1,16 @@
 """Decode attention where its passes change form: record counts around the
-merge's rounds.  Outputs are held to the per-element bound of
+merge's rounds, tile counts around a wave's share, and K and V that are not
+finite.  Finite outputs are held to the per-element bound of
 tests/attn_tolerance.py against the float64 oracle."""
 
+import numpy as np
 import pytest
+import torch
 
+from paper_2504_03775_amd import flowkv as fk
 from tests.gpu_helpers import BM, LM
-from tests.test_attention_gpu import run_case, say
-from workloads import Geometry
+from tests.test_attention_gpu import bf16_to_f64, run_case, say
+from workloads import Geometry, make_device_pool
 
 pytestmark = pytest.mark.gpu
 
@@ -25,3 +29,60 @@ def test_merge_at_its_record_counts(dh, records):
     for hq in (2, 8):
         run_case(geom, (LM, BM)[records % 2], sum(-(-t // 16) for t in lens) + 3, lens, hq,
                  900 + records, split, host_lens=bool(hq == 8))
+
+
+# tiles of 32 tokens, four waves: shares of 0, 1 and 2 tiles, full and ragged
+@pytest.mark.parametrize("dh,group", [(64, 1), (64, 8), (128, 2), (128, 8)])
+@pytest.mark.parametrize("split", [0, 1024])
+def test_tile_counts_of_a_wave(dh, group, split):
+    geom = Geometry("tiles", 2, 2, dh, 7, "bfloat16")
+    lens = [1, 31, 32, 33, 96, 97, 127, 128, 129, 160, 255, 256, 257]
+    say(f"tiles: head_dim {dh}, group {group}, split {split}")
+    run_case(geom, BM, sum(-(-t // 7) for t in lens) + 3, lens, 2 * group, 950 + dh + group, split)
+
+
+@pytest.mark.parametrize("dh,group,split", [(128, 8, 0), (128, 8, 64), (128, 4, 0), (64, 2, 0)])
+def test_values_that_are_not_finite(dh, group, split):
+    """An infinite V gives an infinite output (of the heaviest token too, whose
+    weight has zero lower parts), opposite infinities and NaN give NaN, and a
+    score of -inf weighs nothing; the other dims are untouched."""
+    T, bs = 150, 16
+    geom = Geometry("inf", 1, 1, dh, bs, "bfloat16")
+    B = -(-T // bs)
+    t = make_device_pool(geom, BM, B, "cuda", 77)[0]     # (B, 1, 2, bs, 1, dh)
+    q = torch.randn((1, group, dh), generator=torch.Generator("cuda").manual_seed(5),
+                    device="cuda").to(torch.bfloat16)
+    q[:, :, 3] = 1.0
+    k, v = t[:, 0, 0, :, 0].reshape(-1, dh), t[:, 0, 1, :, 0].reshape(-1, dh)
+    scores = bf16_to_f64(q[0]) @ bf16_to_f64(k).T[:, :T] / np.sqrt(dh)
+    top, other = int(scores[0].argmax()), 40
+    assert top != other
+    for tok, dim, val in ((top, 5, np.inf), (other, 6, -np.inf), (top, 7, np.inf),
+                          (other, 7, -np.inf), (90, 9, np.nan)):
+        t[tok // bs, 0, 1, tok % bs, 0, dim] = val
+    t[70 // bs, 0, 0, 70 % bs, 0, 3] = -np.inf           # score -inf: q there is 1
+    pool = fk.KVPool(BM, [t])
+    out = torch.full((1, group, dh), 3.0, device="cuda")
+    ws = torch.empty(max(1, fk.flowkv_decode_attention_workspace(1, group, dh, T, split)),
+                     dtype=torch.uint8, device="cuda")
+    fk.flowkv_decode_attention(pool, 0, q, torch.arange(B, dtype=torch.int32, device="cuda")[None],
+                               torch.tensor([T], dtype=torch.int32, device="cuda"), T,
+                               1 / np.sqrt(dh), out, ws, split)
+    got = out.cpu().numpy()[0].astype(np.float64)
+    k, v = bf16_to_f64(t[:, 0, 0, :, 0].reshape(-1, dh))[:T], bf16_to_f64(
+        t[:, 0, 1, :, 0].reshape(-1, dh))[:T]
+    s = bf16_to_f64(q[0]) @ np.where(np.isinf(k), 0, k).T / np.sqrt(dh)
+    s[:, 70] = -np.inf
+    p = np.exp(s - s.max(1, keepdims=True))
+    p /= p.sum(1, keepdims=True)
+    with np.errstate(invalid="ignore"):
+        want = np.stack([(p[h][:, None] * v).sum(0) for h in range(group)])
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.array_equal(np.isposinf(got), np.isposinf(want))
+    assert np.array_equal(np.isneginf(got), np.isneginf(want))
+    fin = np.isfinite(want)
+    assert fin.sum() == group * (dh - 4)
+    # roundings of 2^-24 on sums of at most sum p |V| ~ 1, a score's own (2^-24 x
+    # sum |q k| ~ 10) moving a weight by as much: about 20 x 2^-24, and four times that
+    # as the bound
+    assert np.abs(got[fin] - want[fin]).max() < 20 * 2.0 ** -24 * 4
