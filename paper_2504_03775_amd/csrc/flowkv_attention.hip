@@ -14,8 +14,9 @@
 // Work split (flash-decoding style):
 //   pass 1: one workgroup of four waves per (KV head, token split, request),
 //           on the matrix cores for every head count: split_pass, below.
-//   pass 2: one workgroup per (query head, request) merges the splits,
-//           several splits per thread in flight.
+//   pass 2: one wave or workgroup per (query head, request) merges the
+//           splits, several splits per thread in flight; not launched where
+//           one split covers the longest request.
 // The grid covers every split up to the longest request.  When the caller
 // passes the lengths on the host they ride in the kernel arguments (the
 // kLens instantiations): a split past its request's end then leaves before
@@ -107,11 +108,17 @@ __device__ __forceinline__ f32x2u* record_ml(const AttnArgs& a, int dh, int64_t 
 // still leaves a record, an empty partial (max -inf, sum 0) for each of its
 // kG query heads, so that the merge reads every split up to max_splits
 // without the request's length.  Its weighted-V part is never written; the
-// merge ignores it.
-template <int kG, int kDh>
-__device__ __forceinline__ void write_empty_partial(const AttnArgs& a, int g, int split, int r,
-                                                    int tid) {
-  if (tid < kG) *record_ml(a, kDh, record_at(a, r, g * kG + tid, split)) = f32x2u{-INFINITY, 0.f};
+// merge ignores it.  Where pass 1 writes the output itself, a request with no
+// token gets zeros.
+template <int kG, int kDh, bool kDirect>
+__device__ __forceinline__ void write_past_end(const AttnArgs& a, int g, int split, int r,
+                                               int tid) {
+  if constexpr (kDirect) {
+    for (int i = tid; i < kG * kDh; i += kThreads)
+      a.out[(int64_t(r) * a.q_heads + g * kG) * kDh + i] = 0.f;
+  } else if (tid < kG) {
+    *record_ml(a, kDh, record_at(a, r, g * kG + tid, split)) = f32x2u{-INFINITY, 0.f};
+  }
 }
 
 template <int kW> struct Words;
@@ -175,11 +182,14 @@ __device__ __forceinline__ uint32_t pair_lo(uint32_t lo, uint32_t hi) {
 // against 21.1; 16 x 32,000, G 8, one KV head, 47.8 against 55.0; head_dim 64,
 // 32 of 1,000-4,000, G 8, 46.2 against 84.8.
 //
+// kDirect: one split covers the longest request, and this pass writes the
+// output (a flag read at run time cost every other call 0.4 us).
+//
 // kVLds: V waits in LDS instead of in registers (global_load_lds).  The
 // compiler does not track these loads for LDS reads, so the wave waits for
 // them explicitly: for all of them at the top of a step, where the tile's V
 // moves to registers and frees the buffer.
-template <int kDh, int kG, bool kLM, bool kLens, bool kVLds>
+template <int kDh, int kG, bool kLM, bool kLens, bool kVLds, bool kDirect>
 __device__ __forceinline__ void split_pass(const AttnArgs& a) {
   constexpr int kTile = 32;                      // tokens per wave step
   constexpr int kI = kDh / 32;                   // MFMA steps of K.q
@@ -200,10 +210,10 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
   const int bs = a.block_size;
   // with the length in the arguments, a split past the request's end leaves
   // at once, before any memory access, and writes no record
-  if constexpr (kLens)
+  if constexpr (kLens && !kDirect)
     if (t0 >= clamp_len(a, a.lens[r])) return;
   if (t0 >= a.max_blocks * bs) {
-    write_empty_partial<kG, kDh>(a, g, split, r, tid);
+    write_past_end<kG, kDh, kDirect>(a, g, split, r, tid);
     return;
   }
   // the byte offset of every token's row in the pool, staged once in LDS; a
@@ -235,7 +245,7 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
   }
   const int T = clamp_len(a, kLens ? a.lens[r] : a.seq_lens[r]);
   if (t0 >= T) {  // uniform: this split is past the request's end (no kLens)
-    write_empty_partial<kG, kDh>(a, g, split, r, tid);
+    write_past_end<kG, kDh, kDirect>(a, g, split, r, tid);
     return;
   }
   const int n_tok = t0 + a.split_tokens < T ? a.split_tokens : T - t0;
@@ -480,7 +490,8 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
       s_w[w][tid] = wt;
       L = fmaf(s_l[w][tid], wt, L);
     }
-    *record_ml(a, kDh, record_at(a, r, g * kG + tid, split)) = f32x2u{M, L};
+    if constexpr (kDirect) s_l[0][tid] = L;
+    else *record_ml(a, kDh, record_at(a, r, g * kG + tid, split)) = f32x2u{M, L};
   }
   __syncthreads();
   for (int i = tid; i < kG * kDh; i += kThreads) {
@@ -488,18 +499,23 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
     float A = 0.f;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) A = fmaf(s_o[(w * kG + h) * kDh + d], s_w[w][h], A);
-    record_sums(a, kDh, record_at(a, r, g * kG + h, split))[d] = A;
+    if constexpr (kDirect) {
+      const float L = s_l[0][h];
+      a.out[(int64_t(r) * a.q_heads + g * kG + h) * kDh + d] = L > 0.f ? A / L : 0.f;
+    } else {
+      record_sums(a, kDh, record_at(a, r, g * kG + h, split))[d] = A;
+    }
   }
 }
 
 template <int kG, bool kLM, bool kLens>
 __global__ __launch_bounds__(kThreads, 2) void decode_attn_split_mfma(const AttnArgs a) {
-  split_pass<128, kG, kLM, kLens, true>(a);
+  split_pass<128, kG, kLM, kLens, true, false>(a);
 }
 
-template <int kDh, int kG, bool kLM, bool kLens>
+template <int kDh, int kG, bool kLM, bool kLens, bool kDirect>
 __global__ __launch_bounds__(kThreads, kDh == 64 ? 4 : 3) void decode_attn_split(const AttnArgs a) {
-  split_pass<kDh, kG, kLM, kLens, false>(a);
+  split_pass<kDh, kG, kLM, kLens, false, kDirect>(a);
 }
 
 // Pass 2: the splits' records of one (query head, request), by one wave (up to
@@ -616,21 +632,26 @@ __global__ __launch_bounds__(kMergeThreads) void decode_attn_merge(const AttnArg
 
 using SplitFn = void (*)(AttnArgs);
 
-template <int D, bool LM, bool L>
+template <int D, bool LM, bool L, bool O>
 SplitFn pick_group(int G) {
   switch (G) {
-    case 1: return decode_attn_split<D, 1, LM, L>;
-    case 2: return decode_attn_split<D, 2, LM, L>;
-    case 4: return decode_attn_split<D, 4, LM, L>;
-    default: return decode_attn_split<D, 8, LM, L>;
+    case 1: return decode_attn_split<D, 1, LM, L, O>;
+    case 2: return decode_attn_split<D, 2, LM, L, O>;
+    case 4: return decode_attn_split<D, 4, LM, L, O>;
+    default: return decode_attn_split<D, 8, LM, L, O>;
   }
 }
 
+template <bool L, bool O>
+SplitFn pick_shape(int D, int G, bool lm) {
+  if (D == 64) return lm ? pick_group<64, true, L, O>(G) : pick_group<64, false, L, O>(G);
+  return lm ? pick_group<128, true, L, O>(G) : pick_group<128, false, L, O>(G);
+}
+
 template <bool L>
-SplitFn pick_split_lens(int D, int G, bool lm, bool v_lds) {
+SplitFn pick_split_lens(int D, int G, bool lm, bool direct, bool v_lds) {
   if (v_lds) return lm ? decode_attn_split_mfma<8, true, L> : decode_attn_split_mfma<8, false, L>;
-  if (D == 64) return lm ? pick_group<64, true, L>(G) : pick_group<64, false, L>(G);
-  return lm ? pick_group<128, true, L>(G) : pick_group<128, false, L>(G);
+  return direct ? pick_shape<L, true>(D, G, lm) : pick_shape<L, false>(D, G, lm);
 }
 
 // `fixed_split`: the caller gave split_tokens.  Such calls with 8 query heads
@@ -638,9 +659,10 @@ SplitFn pick_split_lens(int D, int G, bool lm, bool v_lds) {
 // are checked against the emitted code; the default split takes the register
 // form, 5-12% faster (47.5 against 49.7 us on 16 x 32,000 tokens of one KV
 // head, 40.3 against 46.1 on 16 x 1,000-4,000 of eight).
-SplitFn pick_split(int D, int G, bool lm, bool lens, bool fixed_split) {
-  const bool v_lds = D == 128 && G == 8 && fixed_split;
-  return lens ? pick_split_lens<true>(D, G, lm, v_lds) : pick_split_lens<false>(D, G, lm, v_lds);
+SplitFn pick_split(int D, int G, bool lm, bool lens, bool direct, bool fixed_split) {
+  const bool v_lds = D == 128 && G == 8 && fixed_split && !direct;
+  return lens ? pick_split_lens<true>(D, G, lm, direct, v_lds)
+              : pick_split_lens<false>(D, G, lm, direct, v_lds);
 }
 
 template <int D, bool L>
@@ -885,19 +907,23 @@ int launch_attention(const flowkv_pool* pool, int32_t layer, const void* q_dev, 
   a.max_splits = int32_t((int64_t(max_seq_len) + split_tokens - 1) / split_tokens);
   a.max_seq_len = max_seq_len;
   a.scale_log2 = scale * kLog2e;
+  // a call whose longest request is one split needs no merge: pass 1 divides
+  // and writes the output, which saves a launch (one request of 200 tokens
+  // 7.5 against 5.0 us, 64 of 100 at 8 heads per KV head 13.2 against 9.4)
+  const bool direct = a.max_splits == 1;
   if (lens)
     for (int32_t i = 0; i < n_req; ++i) a.lens[i] = seq_lens_host[i];
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   void* args[] = {&a};
   hipError_t e = hipSuccess;
   if (a.max_splits > 0) {
-    SplitFn fn = pick_split(head_dim, G, lm, lens, fixed_split);
+    SplitFn fn = pick_split(head_dim, G, lm, lens, direct, fixed_split);
     e = hipLaunchKernel(reinterpret_cast<const void*>(fn),
                         dim3(unsigned(kv_heads), unsigned(a.max_splits), unsigned(n_req)),
                         dim3(kThreads),
                         args, 0, st);
   }
-  if (e == hipSuccess) {
+  if (e == hipSuccess && !direct) {
     // one wave per (query head, request) where its lane groups hold every
     // record at once, a workgroup's four waves above
     const bool one = a.max_splits <= kMergeChunk * 64 * 4 / head_dim;

@@ -86,3 +86,28 @@ def test_values_that_are_not_finite(dh, group, split):
     # sum |q k| ~ 10) moving a weight by as much: about 20 x 2^-24, and four times that
     # as the bound
     assert np.abs(got[fin] - want[fin]).max() < 20 * 2.0 ** -24 * 4
+
+
+@pytest.mark.parametrize("dh,group", [(64, 4), (128, 8)])
+@pytest.mark.parametrize("host", [False, True])
+def test_one_split_writes_every_output(dh, group, host):
+    """Where no merge runs, a request without tokens still gets zeros, and a
+    request's output is the one it has beside longer ones (which do merge, of
+    one record)."""
+    geom = Geometry("one", 1, 2, dh, 16, "bfloat16")
+    pool = fk.KVPool(LM, make_device_pool(geom, LM, 64, "cuda", 31))
+    lens = np.array([0, 256, 1, 100], np.int32)
+    tab = torch.randperm(64, dtype=torch.int32, generator=torch.Generator().manual_seed(3)
+                         ).reshape(4, 16).cuda()
+    q = torch.randn((4, 2 * group, dh), generator=torch.Generator("cuda").manual_seed(4),
+                    device="cuda").to(torch.bfloat16)
+    outs = []
+    for top in (256, 257):                  # one split of 256 tokens, then two
+        out = torch.full((4, 2 * group, dh), float("nan"), device="cuda")
+        ws = torch.empty(fk.flowkv_decode_attention_workspace(4, 2 * group, dh, top),
+                         dtype=torch.uint8, device="cuda")
+        fk.flowkv_decode_attention(pool, 0, q, tab, torch.as_tensor(lens, device="cuda"), top,
+                                   0.1, out, ws, seq_lens_host=lens if host else None)
+        outs.append(out.cpu())
+    assert (outs[0][0] == 0).all()
+    assert torch.equal(outs[0], outs[1])
