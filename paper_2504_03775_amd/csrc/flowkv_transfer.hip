@@ -510,7 +510,8 @@ bool contiguous_plan(const flowkv_segment* r, int64_t n, int64_t total_blocks) {
 }
 
 // Library defaults, from interleaved launch-shape comparisons over the five
-// transfer workloads in both layouts: 1024 threads moving 4 vectors each per
+// transfer workloads in both layouts: 1024 threads (small copies and short
+// blocks: default_threads, below) moving 4 vectors each per
 // tile (64 KiB tiles), nontemporal loads and stores, one tile per workgroup.
 // Visiting order: in plan order the resident workgroups of block-major pools
 // stream one contiguous window of each pool, which ran 7-11% slower on the
@@ -527,6 +528,29 @@ constexpr int kDefaultOrder = 2;    // blocks scattered
 constexpr int kDefaultOrderBM = 4;  // both pools block-major: tile-major
 constexpr uint64_t kPermPrime = 2654435761ull;
 constexpr int64_t kMaxGridPerCU = 2048;
+
+// Workgroup size where the caller leaves the launch shape to the library; all
+// sizes keep four vectors per lane.  What bounds a small copy is a launch and
+// too few waves, not bandwidth, and a 1024-thread workgroup starts slowly.
+// - Up to 8 MiB in all, 64 KiB tiles would be at most 128 on 256 CUs: 128
+//   threads (8 KiB tiles).  One MI355X, 20 launches in a graph, 1024 against
+//   128 threads: 256 KiB 3.9 against 3.1 us, one layer of 60 blocks (3.8 MiB)
+//   5.3 against 4.4, of 125 (7.8 MiB) 6.3 against 5.6; of 250 (15.6 MiB) the
+//   other way, 8.7 against 9.1.
+// - Above, where a block's span fills one line of 1024 threads at most (16
+//   KiB), such a workgroup had one vector per lane: 256 threads carry the span
+//   with four.  1,024 blocks of 16 KiB 10.9 against 8.2 us, 2,000 of 14 KiB
+//   18.4 against 12.4.  From 56 KiB to a full tile 1024 threads are within 4%
+//   either way on 16-130 MiB, and 10% ahead on 260 MiB and more.
+constexpr int64_t kSmallBytes = int64_t(8) << 20;
+constexpr int kSmallThreads = 128;
+constexpr int64_t kShortSpan = int64_t(kDefaultThreads) * 16;
+constexpr int kShortSpanThreads = kDefaultThreads / kDefaultUnroll;
+
+int default_threads(int64_t total_blocks, int64_t span) {
+  if (total_blocks <= kSmallBytes / span) return kSmallThreads;  // (no product: it could overflow)
+  return span <= kShortSpan ? kShortSpanThreads : kDefaultThreads;
+}
 
 std::atomic<int> g_cu_count[64];
 
@@ -636,6 +660,10 @@ int launch_transfer(const flowkv_pool* src, const flowkv_pool* dst,
     if (cfg->order) order = cfg->order;
     grid = cfg->grid;
   }
+  // the shape is the library's only where the caller gave no part of it
+  const bool own_shape = !cfg || (!cfg->threads && !cfg->unroll && !cfg->grid);
+  if (own_shape && total_blocks > 0 && layer_count > 0)
+    threads = default_threads(total_blocks, 2 * int64_t(layer_count) * src->chunk_bytes);
   if (order < 1 || order > 4) return fail(FLOWKV_EINVAL, "order %d: need 1..4", order);
   if (threads < 64 || threads > 1024 || threads % 64)
     return fail(FLOWKV_EINVAL, "threads %d: need a multiple of 64 in 64..1024", threads);

@@ -109,6 +109,24 @@ def test_random_shapes_layouts_and_launch_shapes(seed):
     check_full_pool(geom, sl, dl, Bs, Bd, tables, seed=seed, **cfg)
 
 
+# blocks of 16 KiB (the longest that 256 threads take), of 17 KiB and of 2,400
+# bytes (no whole line per chunk), on both sides of 8 MiB in all
+@pytest.mark.parametrize("L,hkv,dh,bs", [(2, 2, 64, 16), (2, 2, 64, 17), (3, 1, 40, 5)])
+@pytest.mark.parametrize("past", [0, 1])
+@pytest.mark.parametrize("inline", [False, True])
+def test_default_launch_shapes_at_their_edges(L, hkv, dh, bs, past, inline):
+    geom = Geometry("shape", L, hkv, dh, bs, "bfloat16")
+    n = (8 << 20) // geom.block_bytes + past
+    g = np.random.default_rng(n)
+    if inline:         # one run; lists in any order do not fit the arguments
+        S, D = np.arange(7, 7 + n, dtype=np.int32), np.arange(n, dtype=np.int32)
+    else:
+        S, D = (g.permutation(n + 9)[:n].astype(np.int32) for _ in range(2))
+    for sl, dl in LAYOUT_PAIRS:
+        say(f"shape block={geom.block_bytes} n={n} {NAMES[sl]}->{NAMES[dl]} inline={inline}")
+        check_full_pool(geom, sl, dl, n + 9, n + 9, [(S, D)], inline=inline)
+
+
 def test_empty_plan_leaves_pool_unchanged():
     src = device_pool(TINY, BM, 8, 0)
     dst = device_pool(TINY, LM, 8, 1)
