@@ -16,14 +16,12 @@ three sources, each scaled by a quantity the oracle returns beside the output
       of absolute products, s1, independently: spread sqrt(N_S) * u * s1;
       after normalisation by the sum of weights, twice that;
     - the exponential, the rescale factors and the scale product: 4 u;
-    - in the matrix-core pass, the weight enters P.V as bf16(P) + bf16(P -
-      bf16(P)), a relative 2^-16.
+    - at 8 query heads per KV head, 2^-16 for a weight carried as bf16(P) +
+      bf16(P - bf16(P)) (three parts, which hold it exactly, stay within).
 * The weighted sums of V and of the weights themselves accumulate in float32
   along chains of at most N_A = min(split, T) + ceil(T / split) + 64
-  additions: at most one per token of a split in any lane's chain (the vector
-  pass's lanes
-  take split / 8 tokens or fewer; the matrix-core pass's 32-token tiles take
-  split / 128 x 2 MFMAs of 32 products each), one per split in the merge,
+  additions: at most one per token of a split in any lane's chain (the
+  32-token tiles take split / 128 x 3 MFMAs of 32 products each), one per split in the merge,
   and 64 for the row, wave and set merges.  Every partial sum is bounded by
   w1 = sum p |V|, so rounding errors of size u per addition, independent,
   spread to u * sqrt(N_A) * w1.

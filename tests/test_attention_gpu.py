@@ -331,8 +331,8 @@ def test_blocks_outside_the_pool_contribute_nothing(layout, hq):
     """A block ID outside the pool (negative or >= the pool's size) inside a
     request's length is skipped: the output equals attention over the tokens
     of the valid blocks alone (attention does not depend on token order).
-    8 query heads on 2 KV heads run the vector pass, 16 the matrix-core pass
-    (where a hole falls inside a 32-token tile, split 64: two tiles)."""
+    8 query heads on 2 KV heads keep V in registers, 16 in LDS (a hole falls
+    inside a 32-token tile; split 64: two tiles)."""
     geom = Geometry("holes", 3, 2, 128, 16, "bfloat16")
     B, layer, bs = 50, 1, 16
     pool = fk.KVPool(layout, make_device_pool(geom, layout, B, "cuda", 21))
