@@ -13,7 +13,7 @@
 // and the work per token is kept small enough that the loads stay the limit.
 // Work split (flash-decoding style):
 //   pass 1: one workgroup of four waves per (KV head, token split, request),
-//           on the matrix cores for every head count: split_pass, below.
+//           on the matrix cores for every head count (decode_attn_split).
 //   pass 2: one wave or workgroup per (query head, request) merges the
 //           splits, several splits per thread in flight; not launched where
 //           one split covers the longest request.
@@ -176,7 +176,7 @@ __device__ __forceinline__ uint32_t pair_lo(uint32_t lo, uint32_t hi) {
 // limit at 8 heads, and at head_dim 64).  A CU alone draws about 40 bytes a
 // nanosecond, with four waves or eight; all together reach 5.9 TB/s at 8 KV
 // heads, 6.5 at one.  Registers (158 a lane at Dh 128) allow three workgroups
-// per CU, at Dh 64 (102) five.  Both passes, this form against the one before
+// per CU, at Dh 64 (102, taken as 104) four.  Both passes, this form against the one before
 // (events around graphs, one MI355X): 32 requests of 2,000-20,000 tokens, G 4,
 // 246 against 250 us; 48 of 30-1,500, 36.6 against 46.5; one of 13,000, 16.6
 // against 21.1; 16 x 32,000, G 8, one KV head, 47.8 against 55.0; head_dim 64,
@@ -184,13 +184,8 @@ __device__ __forceinline__ uint32_t pair_lo(uint32_t lo, uint32_t hi) {
 //
 // kDirect: one split covers the longest request, and this pass writes the
 // output (a flag read at run time cost every other call 0.4 us).
-//
-// kVLds: V waits in LDS instead of in registers (global_load_lds).  The
-// compiler does not track these loads for LDS reads, so the wave waits for
-// them explicitly: for all of them at the top of a step, where the tile's V
-// moves to registers and frees the buffer.
-template <int kDh, int kG, bool kLM, bool kLens, bool kVLds, bool kDirect>
-__device__ __forceinline__ void split_pass(const AttnArgs& a) {
+template <int kDh, int kG, bool kLM, bool kLens, bool kDirect>
+__global__ __launch_bounds__(kThreads, kDh == 64 ? 4 : 3) void decode_attn_split(const AttnArgs a) {
   constexpr int kTile = 32;                      // tokens per wave step
   constexpr int kI = kDh / 32;                   // MFMA steps of K.q
   constexpr int kT = kDh / 16;                   // dims a lane owns in P.V
@@ -198,8 +193,6 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
   constexpr int kPc = kDh / 8;                   // 16-byte pieces of a K row
   constexpr int kKL = kTile * kPc / 64;          // K loads of a tile and lane
   constexpr int kTileBytes = kTile * kDh * 2;
-  constexpr int kIssueVm = kKL + 8;              // loads of one tile
-  static_assert(kIssueVm < 64, "the wait count must fit the 6-bit vector-memory counter");
   using VT = typename Words<kVW>::T;
   const int g = blockIdx.x, split = blockIdx.y, r = blockIdx.z;
   const int tid = threadIdx.x, ln = tid & 63;
@@ -268,12 +261,6 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
   const uint32_t sstride = uint32_t(a.kv_heads) * kDh * 2;
   kbase += g * kDh * 2;
 
-  if constexpr (kVLds) {
-    // one wait for everything above: the loop's is then the only partial one
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0)
-    __builtin_amdgcn_sched_barrier(0);
-  }
 #pragma unroll
   for (int i = 0; i < kStage; ++i) {
     const int x = tid + i * kThreads;
@@ -286,12 +273,11 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
     }
   }
 
-  // a tile per wave: K's staging and, with kVLds, V's buffer; after the loop
-  // the area holds the waves' weighted sums
+  // K's staging, a tile per wave; after the loop the area holds the waves'
+  // weighted sums
   __shared__ __attribute__((aligned(16))) uint8_t s_area[kWaves * kTileBytes];
   static_assert(sizeof(float) * kWaves * kG * kDh <= sizeof(s_area), "merge area fits");
-  uint8_t* const my_area = s_area + wave * kTileBytes;
-  u32x4* const s_k = reinterpret_cast<u32x4*>(my_area);
+  u32x4* const s_k = reinterpret_cast<u32x4*>(s_area + wave * kTileBytes);
 
   f32x4 o[kT];
 #pragma unroll
@@ -313,34 +299,18 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
   };
   auto load_v = [&](int tile, bool real) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const char* p =
-          kbase + voff + c16 * (kVW * 4) + s_off[real ? tile * kTile + 8 * q4 + e : 0];
-      if constexpr (kVLds)
-        __builtin_amdgcn_global_load_lds(
-            (const __attribute__((address_space(1))) void*)p,
-            (__attribute__((address_space(3))) void*)(my_area + e * 1024), 16, 0, 0);
-      else
-        vw[e] = Words<kVW>::load_nt(p);
-    }
+    for (int e = 0; e < 8; ++e)
+      vw[e] = Words<kVW>::load_nt(kbase + voff + c16 * (kVW * 4) +
+                                  s_off[real ? tile * kTile + 8 * q4 + e : 0]);
   };
   if (wave < n_tiles) {
-    if constexpr (kVLds) load_v(wave, true);
     load_k(wave, true);
-    if constexpr (!kVLds) load_v(wave, true);
+    load_v(wave, true);
   }
   for (int tile = wave; tile < n_tiles; tile += kWaves) {
     const bool more = tile + kWaves < n_tiles;
-    if constexpr (kVLds) {
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_waitcnt(0x0F70);        // vmcnt(0): this tile's V is in LDS
-      asm volatile("" ::: "memory");
-#pragma unroll
-      for (int e = 0; e < 8; ++e) vw[e] = *reinterpret_cast<const VT*>(my_area + e * 1024 + ln * 16);
-    }
 #pragma unroll
     for (int e = 0; e < kKL; ++e) s_k[(kt + e) * kPc + (kp ^ swz(kt + e))] = kw[e];
-    if constexpr (kVLds) load_k(tile + kWaves, more);
     __builtin_amdgcn_wave_barrier();
     const int kr[2] = {8 * (c16 >> 2) + (c16 & 3), 8 * (c16 >> 2) + 4 + (c16 & 3)};
     bf16x8 ka[2][kI];
@@ -350,11 +320,6 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
       for (int i = 0; i < kI; ++i)
         ka[gg][i] =
             __builtin_bit_cast(bf16x8, s_k[kr[gg] * kPc + ((4 * i + q4) ^ swz(kr[gg]))]);
-    if constexpr (kVLds) {
-      // K's operand is out of the buffer before V's next tile lands in it
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      load_v(tile + kWaves, more);
-    }
     f32x4 s[2];
 #pragma unroll
     for (int gg = 0; gg < 2; ++gg) {
@@ -367,7 +332,7 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
       else s[gg] = si[0] + si[1];
     }
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (!kVLds) load_k(tile + kWaves, more);
+    load_k(tile + kWaves, more);
     __builtin_amdgcn_sched_barrier(0);
     // bit e: the lane's token e of this tile is dead
     uint32_t dead = __builtin_amdgcn_readfirstlane(s_dead[tile]);
@@ -435,8 +400,6 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
         if (dead >> e & 1) vw[e] = VT{};
     }
     __builtin_amdgcn_sched_barrier(0);
-    // this tile's V has landed: only the next tile's loads may be in flight
-    if constexpr (kVLds) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kIssueVm) : "memory");
     // two of the lane's dims at a time: their columns of the 8 tokens as B
     // operands, then the three parts of P, smallest first
 #pragma unroll
@@ -457,10 +420,8 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
               o[2 * m + h], 0, 0, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (!kVLds) load_v(tile + kWaves, more);
+    load_v(tile + kWaves, more);
   }
-  // the loads into LDS issued for the tile after the last are still in flight
-  if constexpr (kVLds) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
   // merge the waves: per head a weight exp2(m_wave - M); a wave that saw no
   // token has m = -inf and weighs nothing
@@ -506,16 +467,6 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
       record_sums(a, kDh, record_at(a, r, g * kG + h, split))[d] = A;
     }
   }
-}
-
-template <int kG, bool kLM, bool kLens>
-__global__ __launch_bounds__(kThreads, 2) void decode_attn_split_mfma(const AttnArgs a) {
-  split_pass<128, kG, kLM, kLens, true, false>(a);
-}
-
-template <int kDh, int kG, bool kLM, bool kLens, bool kDirect>
-__global__ __launch_bounds__(kThreads, kDh == 64 ? 4 : 3) void decode_attn_split(const AttnArgs a) {
-  split_pass<kDh, kG, kLM, kLens, false, kDirect>(a);
 }
 
 // Pass 2: the splits' records of one (query head, request), by one wave (up to
@@ -649,20 +600,12 @@ SplitFn pick_shape(int D, int G, bool lm) {
 }
 
 template <bool L>
-SplitFn pick_split_lens(int D, int G, bool lm, bool direct, bool v_lds) {
-  if (v_lds) return lm ? decode_attn_split_mfma<8, true, L> : decode_attn_split_mfma<8, false, L>;
+SplitFn pick_split_lens(int D, int G, bool lm, bool direct) {
   return direct ? pick_shape<L, true>(D, G, lm) : pick_shape<L, false>(D, G, lm);
 }
 
-// `fixed_split`: the caller gave split_tokens.  Such calls with 8 query heads
-// per KV head at head_dim 128 keep V's way through LDS, whose explicit waits
-// are checked against the emitted code; the default split takes the register
-// form, 5-12% faster (47.5 against 49.7 us on 16 x 32,000 tokens of one KV
-// head, 40.3 against 46.1 on 16 x 1,000-4,000 of eight).
-SplitFn pick_split(int D, int G, bool lm, bool lens, bool direct, bool fixed_split) {
-  const bool v_lds = D == 128 && G == 8 && fixed_split && !direct;
-  return lens ? pick_split_lens<true>(D, G, lm, direct, v_lds)
-              : pick_split_lens<false>(D, G, lm, direct, v_lds);
+SplitFn pick_split(int D, int G, bool lm, bool lens, bool direct) {
+  return lens ? pick_split_lens<true>(D, G, lm, direct) : pick_split_lens<false>(D, G, lm, direct);
 }
 
 template <int D, bool L>
@@ -846,7 +789,6 @@ int launch_attention(const flowkv_pool* pool, int32_t layer, const void* q_dev, 
   if (int64_t(max_blocks) * bs > INT32_MAX)
     return fail(FLOWKV_EINVAL, "max_blocks %d x block_size %lld tokens: need at most 2^31 - 1",
                 max_blocks, (long long)bs);
-  const bool fixed_split = split_tokens != 0;
   if (split_tokens == 0) split_tokens = auto_split(n_req, max_seq_len);
   if (split_tokens < 1 || split_tokens > FLOWKV_ATTN_MAX_SPLIT)
     return fail(FLOWKV_EINVAL, "split_tokens %d: need 1..%d", split_tokens,
@@ -917,7 +859,7 @@ int launch_attention(const flowkv_pool* pool, int32_t layer, const void* q_dev, 
   void* args[] = {&a};
   hipError_t e = hipSuccess;
   if (a.max_splits > 0) {
-    SplitFn fn = pick_split(head_dim, G, lm, lens, direct, fixed_split);
+    SplitFn fn = pick_split(head_dim, G, lm, lens, direct);
     e = hipLaunchKernel(reinterpret_cast<const void*>(fn),
                         dim3(unsigned(kv_heads), unsigned(a.max_splits), unsigned(n_req)),
                         dim3(kThreads),

@@ -1,17 +1,7 @@
-"""The matrix-core attention pass's explicit vector-memory wait against the
-gfx950 code the compiler emits (CPU: hipcc cross-compiles without a GPU).
-
-Inside its tile loop, decode_attn_split_mfma waits with s_waitcnt
-vmcnt(kIssueVm) for the current tile's V, which it loaded into LDS with
-global_load_lds: the compiler does not track those loads for LDS reads.  That
-wait is right only if the loop issues exactly kIssueVm vector-memory
-instructions per iteration -- the next tile's loads -- and nothing else that
-counts against the same counter (a register spill to scratch would).  The
-immediate comes from the constexpr counts that size the issue loop; this test
-checks the emitted code against it, for both layouts.
-
-The transfer kernels are checked the same way for what the library claims
-of them: every instantiation runs without scratch memory.
+"""The gfx950 code the compiler emits for the kernels (CPU: hipcc
+cross-compiles without a GPU), against what the sources claim of them: every
+instantiation keeps its state in registers, and the attention pass as few of
+them as the workgroups per CU that its comment states.
 """
 
 import os
@@ -23,7 +13,6 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SRC = os.path.join(ROOT, "paper_2504_03775_amd", "csrc", "flowkv_attention.hip")
-VM = re.compile(r"^\s+(global_|buffer_|flat_|scratch_)\w+")
 
 
 def hipcc():
@@ -46,44 +35,38 @@ def asm(tmp_path_factory):
     return out.read_text()
 
 
-def kernel_text(asm, pattern):
-    m = re.search(rf"^({pattern}):[^\n]*\n(.*?)\n\s+s_endpgm", asm, re.S | re.M)
-    assert m, pattern
-    return m.group(1), m.group(2)
+def kernel_entries(asm, kernel):
+    """The code object's kernel list (one YAML entry each), by name."""
+    out = {}
+    for e in re.split(r"\n  - ", asm):
+        m = re.search(rf"\.name:\s+(\S*{kernel}\S*)", e)
+        if m:
+            out[m.group(1)] = e
+    return out
 
 
-def metadata(asm, name):
-    m = re.search(rf"\.name:\s+{re.escape(name)}\n(.*?)(?=\n  - \.|\Z)", asm, re.S)
-    assert m, name
-    return m.group(1)
-
-
-@pytest.mark.parametrize("lens", ["Lb0", "Lb1"], ids=["lengths-on-device", "lengths-in-arguments"])
-@pytest.mark.parametrize("layout", ["Lb0", "Lb1"], ids=["block-major", "layer-major"])
-def test_mfma_wait_matches_the_loads_the_loop_issues(asm, layout, lens):
-    name, body = kernel_text(asm, rf"_ZN\w*decode_attn_split_mfmaILi8E{layout}E{lens}EEEvN\w+")
-    waits = [int(x) for x in re.findall(r"s_waitcnt vmcnt\((\d+)\)", body)]
-    explicit = [w for w in waits if w > 0]
-    assert len(explicit) == 1, waits
-    n = explicit[0]
-    # the basic blocks of the loop that holds the explicit wait: LLVM marks
-    # each with its loop header
-    blocks = re.split(r"\n(?=\.LBB\d+_\d+:)", body)
-    holder = next(b for b in blocks if f"s_waitcnt vmcnt({n})" in b)
-    header = re.search(r"(?:Header=|=>This Inner Loop Header)", holder.split("\n")[0])
-    assert header, "the explicit wait is not inside a loop"
-    m = re.search(r"Header=(BB\d+_\d+)", holder.split("\n")[0])
-    head = m.group(1) if m else holder.split(":")[0].lstrip(".")
-    in_loop = [b for b in blocks
-               if f"Header={head} " in b.split("\n")[0] or b.startswith(f".L{head}:")]
-    assert len(in_loop) >= 2
-    vm = [ln.strip() for b in in_loop for ln in b.split("\n") if VM.match(ln)]
-    assert len(vm) == n, (n, vm)
-    assert sum("global_load_lds" in x for x in vm) == n // 2     # V into LDS
-    assert not any("store" in x or "atomic" in x for x in vm)
-    meta = metadata(asm, name)
-    assert re.search(r"\.private_segment_fixed_size:\s+0\b", meta)
-    assert re.search(r"\.vgpr_spill_count:\s+0\b", meta)
+def test_attention_kernels_use_no_scratch_and_keep_their_occupancy(asm):
+    """Pass 1 is one kernel per head_dim, query heads per KV head, layout,
+    source of the lengths and place of the output, whatever split_tokens is;
+    the merge one per head_dim, source of the lengths and width.  None uses
+    scratch memory or spills, and pass 1's registers (512 a SIMD lane, taken
+    in eights) allow three workgroups of four waves per CU at head_dim 128 and
+    four at 64."""
+    split, merge = kernel_entries(asm, "decode_attn_split"), kernel_entries(asm, "decode_attn_merge")
+    assert len(split) == 2 * 4 * 2 * 2 * 2, sorted(split)
+    assert len(merge) == 2 * 2 * 2, sorted(merge)
+    for n, e in {**split, **merge}.items():
+        assert re.search(r"\.private_segment_fixed_size:\s+0\b", e), n
+        assert re.search(r"\.vgpr_spill_count:\s+0\b", e), n
+        assert int(re.search(r"\.kernarg_segment_size:\s+(\d+)", e).group(1)) <= 4096, n
+    for n, e in split.items():
+        m = re.search(r"decode_attn_splitILi(64|128)E", n)
+        assert m, n
+        waves = 4 if m.group(1) == "64" else 3
+        vgprs = int(re.search(r"\.vgpr_count:\s+(\d+)", e).group(1))
+        lds = int(re.search(r"\.group_segment_fixed_size:\s+(\d+)", e).group(1))
+        assert waves * (-(-vgprs // 8) * 8) <= 512, (n, vgprs)
+        assert waves * lds <= 160 * 1024, (n, lds)
 
 
 # ---- the transfer kernels: no scratch memory, no spills ------------------------
@@ -120,12 +103,9 @@ def test_transfer_kernels_use_no_scratch_and_spill_nothing(xfer_asm):
     assert len(names) == 4 * 4 * 4 * 2 * 2 + 32 + 96, len(names)
     assert sum("XferArgsCompactILi1E" in n for n in names) == 32
     assert sum("XferArgsCompactILi32E" in n for n in names) == 96
-    # the code object's kernel list, one YAML entry per kernel
-    entries = [e for e in re.split(r"\n  - ", xfer_asm) if "kv_segment_copy" in e
-               and re.search(r"\.name:\s+\S*kv_segment_copy", e)]
+    entries = kernel_entries(xfer_asm, "kv_segment_copy")
     assert len(entries) == len(names)
-    for e in entries:
-        n = re.search(r"\.name:\s+(\S+)", e).group(1)
+    for n, e in entries.items():
         assert re.search(r"\.private_segment_fixed_size:\s+0\b", e), n
         assert re.search(r"\.vgpr_spill_count:\s+0\b", e), n
         if "ELi4ELi" in n:    # unroll 4, the default
