@@ -148,14 +148,17 @@ __device__ __forceinline__ uint32_t pair_lo(uint32_t lo, uint32_t hi) {
 // four tiles apart; per tile:
 //   - K and V rows arrive whole: 16 lanes read one token's head vector (Dh 64:
 //     8 lanes for K, 16 of 8 bytes for V), so every instruction reads full
-//     128-byte lines.  A lane of group q4 = lane / 16 holds V of the tokens
-//     8 q4 + e (e = 0..7), dims kT c16 .. + kT (c16 = lane % 16).
+//     128-byte lines, and consecutive tokens: 4 rows a slot apart, of one block
+//     but at a block's edge.  (Rows 8 tokens apart mostly lay in two blocks, which
+//     in a block-major pool are megabytes apart: 1.2% slower on the 32-request
+//     batch, 256.7 against 259.9 us.)  A lane of group q4 = lane / 16 holds V of
+//     the tokens 4 e + q4 (e = 0..7), dims kT c16 .. + kT (c16 = lane % 16).
 //   - K goes through the wave's LDS tile into the A operand, its 16-byte
 //     pieces swizzled so that neither side conflicts.  (Loading the operand
 //     straight from memory reads 64 bytes of 16 tokens per instruction: 4-12%
 //     slower overall, 257.9 against 243.2 us on the 32-request batch.)
 //   - S^T (32 tokens x 16 heads, columns past G zero) = K Q^T by 16x16x32
-//     MFMAs, row m of half gg being token 8 (m / 4) + 4 gg + m % 4: a lane then
+//     MFMAs, row m of half gg being token 16 gg + 4 (m % 4) + m / 4: a lane then
 //     holds, for head c16, the scores of exactly the eight tokens whose V it
 //     holds, in the order of the A operand of P.V.  So P needs no exchange
 //     between lanes, and V's B operand is a transpose inside the lane.
@@ -209,10 +212,11 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
     write_past_end<kG, kDh, kDirect>(a, g, split, r, tid);
     return;
   }
-  // the byte offset of every token's row in the pool, staged once in LDS; a
-  // token past the end or with a block outside the pool reads the pool's
-  // first slot and has its bit set in its tile's mask.  The block IDs are
-  // fetched without waiting for the request's length.
+  // the byte offset of every token's row in the pool, staged once in LDS (of a
+  // tile, token 4 e + q4 at 8 q4 + e); a token past the end or with a block
+  // outside the pool reads the pool's first slot and has its bit set in its
+  // tile's mask.  The block IDs are fetched without waiting for the request's
+  // length.
   __shared__ __attribute__((aligned(16))) int64_t s_off[FLOWKV_ATTN_MAX_SPLIT];
   __shared__ uint32_t s_dead[FLOWKV_ATTN_MAX_SPLIT / kTile];
   constexpr int kStage = FLOWKV_ATTN_MAX_SPLIT / kThreads;
@@ -267,7 +271,7 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
     const bool ok = x < n_tok && blk[i] >= 0 && blk[i] < a.pool_blocks;
     const uint64_t dead = __ballot(!ok);
     if (x < n_tiles * kTile) {
-      s_off[x] =
+      s_off[(x & -kTile) + (x & 3) * 8 + (x >> 2 & 7)] =
           ok ? int64_t(uint64_t(uint32_t(blk[i])) * bstride + uint32_t(slot[i]) * sstride) : 0;
       if (ln % kTile == 0) s_dead[x / kTile] = uint32_t(dead >> ln);
     }
@@ -287,15 +291,19 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
 
   u32x4 kw[kKL];
   VT vw[8];
-  // K loads: lane ln takes piece ln % kPc of the tokens kt + e
-  const int kt = ln / kPc * kKL, kp = ln % kPc;
+  // K loads: lane ln takes piece kp of the tokens kt + e kStride, whose offsets
+  // are at k_at + e kStride / 4
+  constexpr int kStride = 64 / kPc;
+  const int kt = ln / kPc, kp = ln % kPc;
+  const int k_at = (kt & 3) * 8 + (kt >> 2);
   // a row's pieces are XORed with a number that differs among the 16 rows of
-  // one operand read
-  auto swz = [](int token) { return (4 * (token >> 3) + (token & 3)) % kPc; };
+  // one operand read (at Dh 64, where two rows fill the banks, among the 8 pairs)
+  auto swz = [](int token) { return (token * kPc >> 4) & (kPc - 1); };
   auto load_k = [&](int tile, bool real) {
 #pragma unroll
     for (int e = 0; e < kKL; ++e)
-      kw[e] = Words<4>::load_nt(kbase + 16 * kp + s_off[real ? tile * kTile + kt + e : 0]);
+      kw[e] = Words<4>::load_nt(kbase + 16 * kp +
+                                s_off[real ? tile * kTile + k_at + e * (kStride / 4) : 0]);
   };
   auto load_v = [&](int tile, bool real) {
 #pragma unroll
@@ -310,9 +318,12 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
   for (int tile = wave; tile < n_tiles; tile += kWaves) {
     const bool more = tile + kWaves < n_tiles;
 #pragma unroll
-    for (int e = 0; e < kKL; ++e) s_k[(kt + e) * kPc + (kp ^ swz(kt + e))] = kw[e];
+    for (int e = 0; e < kKL; ++e) {
+      const int token = kt + e * kStride;
+      s_k[token * kPc + (kp ^ swz(token))] = kw[e];
+    }
     __builtin_amdgcn_wave_barrier();
-    const int kr[2] = {8 * (c16 >> 2) + (c16 & 3), 8 * (c16 >> 2) + 4 + (c16 & 3)};
+    const int kr[2] = {4 * (c16 & 3) + (c16 >> 2), 16 + 4 * (c16 & 3) + (c16 >> 2)};
     bf16x8 ka[2][kI];
 #pragma unroll
     for (int gg = 0; gg < 2; ++gg)
@@ -334,14 +345,14 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
     __builtin_amdgcn_sched_barrier(0);
     load_k(tile + kWaves, more);
     __builtin_amdgcn_sched_barrier(0);
-    // bit e: the lane's token e of this tile is dead
+    // bit 4 e: the lane's token 4 e + q4 of this tile is dead
     uint32_t dead = __builtin_amdgcn_readfirstlane(s_dead[tile]);
     const bool masked = dead != 0;               // uniform
     if (masked) {
-      dead >>= 8 * q4;
+      dead >>= q4;
 #pragma unroll
       for (int e = 0; e < 8; ++e)
-        if (dead >> e & 1) s[e >> 2][e & 3] = -INFINITY;
+        if (dead >> (4 * e) & 1) s[e >> 2][e & 3] = -INFINITY;
     }
     // scaled scores, rounded before the reference is taken off them (a fused
     // multiply-subtract would leave the largest token a weight other than 1)
@@ -397,7 +408,7 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
     if (masked) {
 #pragma unroll
       for (int e = 0; e < 8; ++e)
-        if (dead >> e & 1) vw[e] = VT{};
+        if (dead >> (4 * e) & 1) vw[e] = VT{};
     }
     __builtin_amdgcn_sched_barrier(0);
     // two of the lane's dims at a time: their columns of the 8 tokens as B
