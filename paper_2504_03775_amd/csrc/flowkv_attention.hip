@@ -166,9 +166,10 @@ __device__ __forceinline__ uint32_t pair_lo(uint32_t lo, uint32_t hi) {
 //     exceeds it by more than kLazy (log2 units), a wave-uniform branch that
 //     is rarely taken after the first tile.
 //   - P is cut into three bf16 parts by truncation, which hold its 24 bits
-//     exactly; O += P3 V + P2 V + P1 V.  The lower parts are kept from zero (by
-//     at most 2^-126), so that an infinite V gives what P V gives and not
-//     0 x inf.  (A tile summed from zero and added to O once cost registers,
+//     exactly; O += P3 V + P2 V + P1 V.  The parts of a weight above zero are kept
+//     from zero by 2^-133, bf16's smallest value, so that an infinite V gives what
+//     P V gives and not 0 x inf; those of a zero weight are zero, so that no V is
+//     large enough to add anything under it.  (A tile summed from zero and added to O once cost registers,
 //     2-4% of a short call, and was no closer to 64 bits over all.)
 //   - the next tile's K loads are issued as soon as q.k has its operand, its V
 //     loads after P.V; past the wave's last tile they read the split's first
@@ -396,12 +397,13 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
         b2[k] = __float_as_uint(r1);
         b3[k] = __float_as_uint(r1 - __uint_as_float(b2[k] & 0xffff0000u));
       }
-      const u16x2 tiny = {0x0080, 0x0080};       // bf16 2^-126 in both halves
+      const u16x2 one = {1, 1};
       p1[i] = pair_hi(b1[0], b1[1]);
+      const u16x2 least = __builtin_elementwise_min(__builtin_bit_cast(u16x2, p1[i]), one);
       p2[i] = __builtin_bit_cast(
-          uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, pair_hi(b2[0], b2[1])), tiny));
+          uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, pair_hi(b2[0], b2[1])), least));
       p3[i] = __builtin_bit_cast(
-          uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, pair_hi(b3[0], b3[1])), tiny));
+          uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, pair_hi(b3[0], b3[1])), least));
     }
     lsum += (lt[0] + lt[1]) + (lt[2] + lt[3]);
     // dead tokens' weight is 0, and 0 x a stale NaN would not be

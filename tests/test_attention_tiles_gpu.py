@@ -1,6 +1,6 @@
 """Decode attention where its passes change form: record counts around the
 merge's rounds, tile counts around a wave's share, and K and V that are not
-finite.  Finite outputs are held to the per-element bound of
+finite or not of one size.  Finite outputs are held to the per-element bound of
 tests/attn_tolerance.py against the float64 oracle."""
 
 import numpy as np
@@ -111,3 +111,65 @@ def test_one_split_writes_every_output(dh, group, host):
         outs.append(out.cpu())
     assert (outs[0][0] == 0).all()
     assert torch.equal(outs[0], outs[1])
+
+
+def one_head_pool(T, dh, seed):
+    """K and V views (tokens, dh) of a one-layer, one-KV-head pool, N(0, 1)."""
+    geom = Geometry("one", 1, 1, dh, 16, "bfloat16")
+    t = make_device_pool(geom, BM, -(-T // 16), "cuda", seed)[0]     # (B, 1, 2, 16, 1, dh)
+    return fk.KVPool(BM, [t]), t
+
+
+def attend(pool, q, T, scale, split, host):
+    n, hq, dh = q.shape
+    blocks = pool.num_blocks
+    tab = torch.arange(blocks, dtype=torch.int32, device="cuda").repeat(n, 1)
+    out = torch.full((n, hq, dh), 3.0, device="cuda")
+    ws = torch.empty(max(1, fk.flowkv_decode_attention_workspace(n, hq, dh, T, split)),
+                     dtype=torch.uint8, device="cuda")
+    lens = np.full(n, T, np.int32)
+    fk.flowkv_decode_attention(pool, 0, q, tab, torch.as_tensor(lens, device="cuda"), T, scale,
+                               out, ws, split, seq_lens_host=lens if host else None)
+    return out.cpu().numpy().astype(np.float64)
+
+
+def put(t, kv, token, dim, val):
+    t[token // 16, 0, kv, token % 16, 0, dim] = val
+
+
+@pytest.mark.parametrize("dh,group", [(64, 1), (64, 8), (128, 2), (128, 4), (128, 8)])
+@pytest.mark.parametrize("split", [0, 32, 64])
+def test_values_far_larger_than_their_weights(dh, group, split):
+    """A weight that is exactly 0 takes nothing of a V of 3e38, one of about
+    2^-115 its share, and an infinite V stays infinite under the smallest
+    weights.  The scores are K's first dim (q is its unit vector), in log2 units:
+    0 for all other tokens, whose weights are then 1."""
+    T = 100
+    pool, t = one_head_pool(T, dh, 55)
+    t[:, 0, 0, :, 0] = 0                                  # K
+    q = torch.zeros((1, group, dh), dtype=torch.bfloat16, device="cuda")
+    q[:, :, 0] = 1.0
+    scale = np.float32(np.log(2.0))
+    scores = np.zeros(T)
+    for token, score, dim, val in ((37, -300, 4, 3e38), (60, -115, 5, 2.0 ** 127),
+                                   (61, -109.5, 6, -2.0 ** 125), (70, -115, 9, np.inf),
+                                   (20, -125, 10, -np.inf)):
+        put(t, 0, token, 0, score)
+        put(t, 1, token, dim, val)
+        scores[token] = score
+    v = bf16_to_f64(t[:, 0, 1, :, 0].reshape(-1, dh))[:T]
+    w = np.exp2(scores * np.float64(scale * np.float32(np.log2(np.e))))
+    w[37] = 0.0                                           # (2^-300 is no float32)
+    with np.errstate(invalid="ignore"):
+        want = (w[:, None] * v).sum(0) / w.sum()
+    for host in (False, True):
+        got = attend(pool, q, T, float(scale), split, host)[0]
+        assert np.array_equal(np.isposinf(got), np.broadcast_to(np.isposinf(want), got.shape))
+        assert np.array_equal(np.isneginf(got), np.broadcast_to(np.isneginf(want), got.shape))
+        fin = np.isfinite(want)
+        # sums of 100 terms of at most |V| ~ 4: 2^-24 x 100 x 4 / 100 a sum, four
+        # sums; for the tiny weights' dims, exp2's argument (2^-24 x 115) and the
+        # parts below bf16's smallest value (2 x 2^-133 of 2^-115)
+        tol = np.full(dh, 16 * 2.0 ** -24)
+        tol[[5, 6]] = np.abs(want[[5, 6]]) * 2.0 ** -16
+        assert np.all(np.abs(got[:, fin] - want[fin]) <= tol[fin])
