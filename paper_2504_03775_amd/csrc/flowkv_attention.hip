@@ -144,6 +144,11 @@ __device__ __forceinline__ uint32_t pair_lo(uint32_t lo, uint32_t hi) {
   return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
 }
 
+// A float truncated to bf16.
+__device__ __forceinline__ float hi_part(float x) {
+  return __uint_as_float(__float_as_uint(x) & 0xffff0000u);
+}
+
 // Pass 1 on the matrix cores.  Each wave takes its own tiles of 32 tokens,
 // four tiles apart; per tile:
 //   - K and V rows arrive whole: 16 lanes read one token's head vector (Dh 64:
@@ -157,34 +162,39 @@ __device__ __forceinline__ uint32_t pair_lo(uint32_t lo, uint32_t hi) {
 //     pieces swizzled so that neither side conflicts.  (Loading the operand
 //     straight from memory reads 64 bytes of 16 tokens per instruction: 4-12%
 //     slower overall, 257.9 against 243.2 us on the 32-request batch.)
-//   - S^T (32 tokens x 16 heads, columns past G zero) = K Q^T by 16x16x32
-//     MFMAs, row m of half gg being token 16 gg + 4 (m % 4) + m / 4: a lane then
-//     holds, for head c16, the scores of exactly the eight tokens whose V it
-//     holds, in the order of the A operand of P.V.  So P needs no exchange
-//     between lanes, and V's B operand is a transpose inside the lane.
+//   - S^T (32 tokens x 16 columns) = K Q^T by 16x16x32 MFMAs, row m of half gg
+//     being token 16 gg + 4 (m % 4) + m / 4: a lane then holds, for one head, the
+//     scores of exactly the eight tokens whose V it holds, in the order of the A
+//     operand of P.V.  So P needs no exchange between lanes, and V's B operand
+//     is a transpose inside the lane.  Each head has kRep columns (its number is
+//     head_of(c16)), one for each part of its weights.
 //   - online softmax: the reference max of a head moves only when some score
 //     exceeds it by more than kLazy (log2 units), a wave-uniform branch that
 //     is rarely taken after the first tile.
 //   - P is cut into three bf16 parts by truncation, which hold its 24 bits
-//     exactly; O += P3 V + P2 V + P1 V.  The parts of a weight above zero are kept
-//     from zero by 2^-133, bf16's smallest value, so that an infinite V gives what
-//     P V gives and not 0 x inf; those of a zero weight are zero, so that no V is
-//     large enough to add anything under it.  (A tile summed from zero and added to O once cost registers,
-//     2-4% of a short call, and was no closer to 64 bits over all.)
+//     exactly, and the columns of a head carry one each: P.V is one MFMA per 16
+//     dims, and each part has sums of its own, joined once per split (of four
+//     columns the last is spare).  With 8 heads there are two columns and two
+//     MFMAs: the second brings the third part to the second's sums.  (Three MFMAs
+//     onto one sum rounded it three times as often.  Against 64 bits: 1.9e-7 for
+//     2.3e-7 on the 32-request batch, 2.0e-7 for 2.6e-7 at 8 heads of 128, 1.6e-7
+//     for 1.8e-7 at head_dim 64.)  The parts of a weight above zero are kept from
+//     zero by 2^-133, bf16's smallest value, so that an infinite V gives what P V
+//     gives and not 0 x inf; those of a zero weight are zero, so that no V is
+//     large enough to add anything under it.
 //   - the next tile's K loads are issued as soon as q.k has its operand, its V
 //     loads after P.V; past the wave's last tile they read the split's first
 //     row, which keeps their count static.
 // What bounds it: HBM, and a CU's own rate.  A step's instructions are a fifth
 // of the time its 16 KB take at 6 TB/s, whatever G is, so one form serves 1 to
-// 8 query heads per KV head (the vector-unit form it replaces was near its ALU
-// limit at 8 heads, and at head_dim 64).  A CU alone draws about 40 bytes a
-// nanosecond, with four waves or eight; all together reach 5.9 TB/s at 8 KV
-// heads, 6.5 at one.  Registers (158 a lane at Dh 128) allow three workgroups
-// per CU, at Dh 64 (102, taken as 104) four.  Both passes, this form against the one before
-// (events around graphs, one MI355X): 32 requests of 2,000-20,000 tokens, G 4,
-// 246 against 250 us; 48 of 30-1,500, 36.6 against 46.5; one of 13,000, 16.6
-// against 21.1; 16 x 32,000, G 8, one KV head, 47.8 against 55.0; head_dim 64,
-// 32 of 1,000-4,000, G 8, 46.2 against 84.8.
+// 8 query heads per KV head.  A CU alone draws about 40 bytes a nanosecond, with
+// four waves or eight.  Registers (166 a lane at Dh 128) allow three workgroups
+// per CU, at Dh 64 (96-98) four are asked for.  Both passes, against the form
+// before this one (vector units up to 4 heads per KV head and at head_dim 64;
+// events around graphs, one MI355X): 32 requests of 2,000-20,000 tokens, G 4,
+// 255.9 us for 258.9; 48 of 30-1,500, 37.9 for 52.5; one of 13,000, 14.5 for
+// 19.8; 16 x 32,000, G 8, one KV head, 45.9 for 49.5; head_dim 64, 24 of
+// 300-6,000, G 2, 22.3 for 26.1.
 //
 // kDirect: one split covers the longest request, and this pass writes the
 // output (a flag read at run time cost every other call 0.4 us).
@@ -197,6 +207,7 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
   constexpr int kPc = kDh / 8;                   // 16-byte pieces of a K row
   constexpr int kKL = kTile * kPc / 64;          // K loads of a tile and lane
   constexpr int kTileBytes = kTile * kDh * 2;
+  constexpr int kRep = kG == 8 ? 2 : 4;          // columns of S, and rows of P, per head
   using VT = typename Words<kVW>::T;
   const int g = blockIdx.x, split = blockIdx.y, r = blockIdx.z;
   const int tid = threadIdx.x, ln = tid & 63;
@@ -232,13 +243,13 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
                         (int32_t(b) < a.max_blocks ? int32_t(b) : a.max_blocks - 1)];
     }
   }
-  // Q as the B operand of K.q: Q[head c16][32 i + 8 q4 .. + 8]; columns past G are zero
+  // Q as the B operand of K.q: Q[head_of(c16)][32 i + 8 q4 .. + 8]
+  auto head_of = [](int column) { return column / kRep % kG; };
   bf16x8 qb[kI];
 #pragma unroll
   for (int i = 0; i < kI; ++i) {
-    u32x4 w = *reinterpret_cast<const u32x4*>(
-        a.q + (int64_t(r) * a.q_heads + g * kG + (c16 < kG ? c16 : 0)) * kDh + 32 * i + 8 * q4);
-    if (c16 >= kG) w = u32x4{0, 0, 0, 0};
+    const u32x4 w = *reinterpret_cast<const u32x4*>(
+        a.q + (int64_t(r) * a.q_heads + g * kG + head_of(c16)) * kDh + 32 * i + 8 * q4);
     qb[i] = __builtin_bit_cast(bf16x8, w);
   }
   const int T = clamp_len(a, kLens ? a.lens[r] : a.seq_lens[r]);
@@ -287,9 +298,12 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
   f32x4 o[kT];
 #pragma unroll
   for (int t = 0; t < kT; ++t) o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float mref = -INFINITY, lsum = 0.f;            // of head c16; the sum of this lane's tokens
+  float mref = -INFINITY, lsum = 0.f;            // of the column's head; this lane's tokens
   __syncthreads();
 
+  // which part the column carries: what is taken off a weight before it
+  const int part = c16 % kRep;
+  const float off1 = part > 0 ? -1.f : 0.f, off2 = part > 1 ? -1.f : 0.f;
   u32x4 kw[kKL];
   VT vw[8];
   // K loads: lane ln takes piece kp of the tokens kt + e kStride, whose offsets
@@ -375,35 +389,43 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
       }
       lsum *= c;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < 4; j += kRep) {        // rows 4 q4 + j .. + kRep: one head
         const float cj = __shfl(c, 4 * q4 + j);
 #pragma unroll
-        for (int t = 0; t < kT; ++t) o[t][j] *= cj;
+        for (int x = j; x < j + kRep; ++x)
+#pragma unroll
+          for (int t = 0; t < kT; ++t) o[t][x] *= cj;
       }
     }
     const float mu = mref == -INFINITY ? 0.f : mref;
-    u32x4 p1, p2, p3;
+    u32x4 pa, pb;                                // the column's part; with 8 heads, the third
     float lt[4];                                 // the tile's sum, in pairs
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
 #pragma clang fp contract(off)
-      uint32_t b1[2], b2[2], b3[2];
+      uint32_t bw[2], ba[2], bb[2];
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
         const float w = __builtin_amdgcn_exp2f(p[2 * i + k] - mu);
         lt[i] = k == 0 ? w : lt[i] + w;
-        b1[k] = __float_as_uint(w);
-        const float r1 = w - __uint_as_float(b1[k] & 0xffff0000u);
-        b2[k] = __float_as_uint(r1);
-        b3[k] = __float_as_uint(r1 - __uint_as_float(b2[k] & 0xffff0000u));
+        bw[k] = __float_as_uint(w);
+        if constexpr (kRep == 2) {
+          const float r1 = w - hi_part(w);
+          ba[k] = __float_as_uint(part > 0 ? r1 : w);
+          bb[k] = __float_as_uint(part > 0 ? r1 - hi_part(r1) : 0.f);
+        } else {
+          const float r1 = fmaf(off1, hi_part(w), w);
+          ba[k] = __float_as_uint(fmaf(off2, hi_part(r1), r1));
+        }
       }
       const u16x2 one = {1, 1};
-      p1[i] = pair_hi(b1[0], b1[1]);
-      const u16x2 least = __builtin_elementwise_min(__builtin_bit_cast(u16x2, p1[i]), one);
-      p2[i] = __builtin_bit_cast(
-          uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, pair_hi(b2[0], b2[1])), least));
-      p3[i] = __builtin_bit_cast(
-          uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, pair_hi(b3[0], b3[1])), least));
+      const u16x2 least =
+          __builtin_elementwise_min(__builtin_bit_cast(u16x2, pair_hi(bw[0], bw[1])), one);
+      pa[i] = __builtin_bit_cast(
+          uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, pair_hi(ba[0], ba[1])), least));
+      if constexpr (kRep == 2)
+        pb[i] = __builtin_bit_cast(
+            uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, pair_hi(bb[0], bb[1])), least));
     }
     lsum += (lt[0] + lt[1]) + (lt[2] + lt[3]);
     // dead tokens' weight is 0, and 0 x a stale NaN would not be
@@ -413,8 +435,7 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
         if (dead >> (4 * e) & 1) vw[e] = VT{};
     }
     __builtin_amdgcn_sched_barrier(0);
-    // two of the lane's dims at a time: their columns of the 8 tokens as B
-    // operands, then the three parts of P, smallest first
+    // two of the lane's dims at a time: their columns of the 8 tokens as B operands
 #pragma unroll
     for (int m = 0; m < kVW; ++m) {
       u32x4 w[2];
@@ -423,14 +444,14 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
         w[0][i] = pair_lo(vw[2 * i][m], vw[2 * i + 1][m]);
         w[1][i] = pair_hi(vw[2 * i][m], vw[2 * i + 1][m]);
       }
-      const u32x4 parts[3] = {p3, p2, p1};
-#pragma unroll
-      for (int k = 0; k < 3; ++k)
+      auto add = [&](u32x4 p) {
 #pragma unroll
         for (int h = 0; h < 2; ++h)
           o[2 * m + h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-              __builtin_bit_cast(bf16x8, parts[k]), __builtin_bit_cast(bf16x8, w[h]),
-              o[2 * m + h], 0, 0, 0);
+              __builtin_bit_cast(bf16x8, p), __builtin_bit_cast(bf16x8, w[h]), o[2 * m + h], 0, 0, 0);
+      };
+      add(pa);
+      if constexpr (kRep == 2) add(pb);
     }
     __builtin_amdgcn_sched_barrier(0);
     load_v(tile + kWaves, more);
@@ -438,7 +459,7 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
 
   // merge the waves: per head a weight exp2(m_wave - M); a wave that saw no
   // token has m = -inf and weighs nothing
-  __shared__ float s_m[kWaves][16], s_l[kWaves][16], s_w[kWaves][16];
+  __shared__ float s_m[kWaves][16], s_l[kWaves][16];
   lsum += __shfl_xor(lsum, 16);
   lsum += __shfl_xor(lsum, 32);
   if (q4 == 0) {
@@ -448,44 +469,59 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
   __syncthreads();  // every wave is past the loop: the area is free
   float* const s_o = reinterpret_cast<float*>(s_area);   // [wave][head < kG][dim]
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-    if (4 * q4 + j < kG) {
+  for (int j = 0; j < 4; j += kRep)              // a head's parts, smallest first
+    if (const int h = (4 * q4 + j) / kRep; h < kG) {
 #pragma unroll
-      for (int t = 0; t < kT; t += 4)
-        *reinterpret_cast<float4*>(&s_o[(wave * kG + 4 * q4 + j) * kDh + kT * c16 + t]) =
-            float4{o[t][j], o[t + 1][j], o[t + 2][j], o[t + 3][j]};
+      for (int t = 0; t < kT; t += 4) {
+        f32x4 x;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const f32x4 y = o[t + k];
+          x[k] = kRep == 2 ? y[j + 1] + y[j] : y[2] + y[1] + y[0];
+        }
+        *reinterpret_cast<f32x4*>(&s_o[(wave * kG + h) * kDh + kT * c16 + t]) = x;
+      }
     }
-  if (tid < kG) {
-    float M = -INFINITY;
-    for (int w = 0; w < kWaves; ++w) M = fmaxf(M, s_m[w][tid]);
-    float L = 0.f;
-    for (int w = 0; w < kWaves; ++w) {
-      const float wt = s_m[w][tid] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s_m[w][tid] - M);
-      s_w[w][tid] = wt;
-      L = fmaf(s_l[w][tid], wt, L);
-    }
-    if constexpr (kDirect) s_l[0][tid] = L;
-    else *record_ml(a, kDh, record_at(a, r, g * kG + tid, split)) = f32x2u{M, L};
-  }
   __syncthreads();
-  for (int i = tid; i < kG * kDh; i += kThreads) {
-    const int h = i / kDh, d = i % kDh;
-    float A = 0.f;
+  // kOut dims of one head per thread
+  constexpr int kOut = kG * kDh > kThreads ? kG * kDh / kThreads : 1;
+  typedef float OutLds __attribute__((ext_vector_type(kOut)));
+  typedef float OutVec __attribute__((ext_vector_type(kOut), aligned(4)));
+  if (tid * kOut >= kG * kDh) return;
+  const int h = tid * kOut / kDh, d = tid * kOut % kDh;
+  float M = -INFINITY, L = 0.f;
+  OutVec A = 0.f;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) A = fmaf(s_o[(w * kG + h) * kDh + d], s_w[w][h], A);
-    if constexpr (kDirect) {
-      const float L = s_l[0][h];
-      a.out[(int64_t(r) * a.q_heads + g * kG + h) * kDh + d] = L > 0.f ? A / L : 0.f;
-    } else {
-      record_sums(a, kDh, record_at(a, r, g * kG + h, split))[d] = A;
-    }
+  for (int w = 0; w < kWaves; ++w) M = fmaxf(M, s_m[w][kRep * h]);
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    const float m = s_m[w][kRep * h];
+    const float wt = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
+    const OutLds x = *reinterpret_cast<const OutLds*>(&s_o[(w * kG + h) * kDh + d]);
+    L = fmaf(s_l[w][kRep * h], wt, L);
+#pragma unroll
+    for (int k = 0; k < kOut; ++k) A[k] = fmaf(x[k], wt, A[k]);
+  }
+  if constexpr (kDirect) {
+#pragma unroll
+    for (int k = 0; k < kOut; ++k) A[k] = L > 0.f ? A[k] / L : 0.f;
+    *reinterpret_cast<OutVec*>(a.out + (int64_t(r) * a.q_heads + g * kG + h) * kDh + d) = A;
+  } else {
+    const int64_t rec = record_at(a, r, g * kG + h, split);
+    *reinterpret_cast<OutVec*>(record_sums(a, kDh, rec) + d) = A;
+    if (d == 0) *record_ml(a, kDh, rec) = f32x2u{M, L};
   }
 }
 
 // (As the kernel's own body, split_pass came out 6% longer, and a 200-token
 // call took 5.4 us for 5.2.)
+// The waves per SIMD are an upper bound too: at Dh 64 the 96 registers would
+// let a fifth workgroup onto a CU while others are idle (24 requests of
+// 300-6,000 tokens 25.8 us for 22.7).
 template <int kDh, int kG, bool kLM, bool kLens, bool kDirect>
-__global__ __launch_bounds__(kThreads, kDh == 64 ? 4 : 3) void decode_attn_split(const AttnArgs a) {
+__global__ __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(kDh == 64 ? 4 : 3, kDh == 64 ? 4 : 3)))
+void decode_attn_split(const AttnArgs a) {
   split_pass<kDh, kG, kLM, kLens, kDirect>(a);
 }
 

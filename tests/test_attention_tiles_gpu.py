@@ -173,3 +173,35 @@ def test_values_far_larger_than_their_weights(dh, group, split):
         tol = np.full(dh, 16 * 2.0 ** -24)
         tol[[5, 6]] = np.abs(want[[5, 6]]) * 2.0 ** -16
         assert np.all(np.abs(got[:, fin] - want[fin]) <= tol[fin])
+
+
+@pytest.mark.parametrize("dh,group", [(64, 2), (64, 8), (128, 1), (128, 4), (128, 8)])
+def test_error_beside_a_float32_evaluation(dh, group):
+    """The error against 64 bits over all outputs of a long request stays within
+    1.6 times that of a float32 evaluation in the pass's own order, which rounds
+    each 32-token tile's sum onto a wave's running sum once (numpy, tiles exact).
+    An MFMA rounds inside its 32 products too, hence the margin: one MFMA per
+    tile and sum measures 1.37-1.45 times, three onto one sum 1.73-2.16."""
+    T, split = 16384, 1024
+    pool, t = one_head_pool(T, dh, 57)
+    q = torch.randn((1, group, dh), generator=torch.Generator("cuda").manual_seed(3),
+                    device="cuda").to(torch.bfloat16)
+    got = attend(pool, q, T, 1 / np.sqrt(dh), split, True)[0]
+    k, v = (bf16_to_f64(t[:, 0, i, :, 0].reshape(-1, dh)) for i in (0, 1))
+    s = bf16_to_f64(q[0]) @ k.T                           # (group, T)
+    scale = np.float64(np.float32(1 / np.sqrt(dh)))
+    p = np.exp(scale * s - (scale * s).max(1, keepdims=True))
+    want = (p @ v) / p.sum(1, keepdims=True)
+    arg = s.astype(np.float32) * np.float32(np.float32(scale) * np.float32(np.log2(np.e)))
+    w = np.exp2(arg - arg.max(1, keepdims=True)).astype(np.float64)
+    # waves take every fourth tile of a split
+    tiles = np.einsum("gntx,ntxd->ngtd", w.reshape(group, -1, 32, 32),
+                      v.reshape(-1, 32, 32, dh)).reshape(-1, group, 8, 4, dh)
+    acc = np.zeros(tiles[:, :, 0].shape, np.float32)
+    for i in range(8):
+        acc = (acc + tiles[:, :, i]).astype(np.float32)
+    f32 = acc.astype(np.float64).sum((0, 2)) / w.sum(1, keepdims=True)
+    kernel, ideal = (np.linalg.norm(x - want) for x in (got, f32))
+    say(f"head_dim {dh}, group {group}: {kernel / np.linalg.norm(want):.2e} against 64 bits, "
+        f"{kernel / ideal:.2f} times a float32 evaluation's")
+    assert kernel <= 1.6 * ideal
