@@ -504,7 +504,7 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
   }
   if constexpr (kDirect) {
 #pragma unroll
-    for (int k = 0; k < kOut; ++k) A[k] = L > 0.f ? A[k] / L : 0.f;
+    for (int k = 0; k < kOut; ++k) A[k] = L == 0.f ? 0.f : A[k] / L;
     *reinterpret_cast<OutVec*>(a.out + (int64_t(r) * a.q_heads + g * kG + h) * kDh + d) = A;
   } else {
     const int64_t rec = record_at(a, r, g * kG + h, split);
@@ -590,7 +590,7 @@ __global__ __launch_bounds__(kMergeThreads) void decode_attn_merge(const AttnArg
     float cm = x.m;
 #pragma unroll
     for (int j = 0; j < kMergeChunk; ++j) {
-      if (x0 + j * kParts >= ns) m[j][0] = -INFINITY;
+      if (x0 + j * kParts >= ns) m[j] = f32x2u{-INFINITY, 0.f};
       cm = fmaxf(cm, m[j][0]);
     }
     const float c = x.m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(x.m - cm);
@@ -598,7 +598,8 @@ __global__ __launch_bounds__(kMergeThreads) void decode_attn_merge(const AttnArg
     x.v *= c;
 #pragma unroll
     for (int j = 0; j < kMergeChunk; ++j) {
-      const bool live = m[j][0] != -INFINITY;
+      // (a split whose scores are all NaN has a max of -inf, and a sum of NaN)
+      const bool live = m[j][0] != -INFINITY || m[j][1] != 0.f;
       const float w = live ? __builtin_amdgcn_exp2f(m[j][0] - cm) : 0.f;
       x.l = live ? fmaf(m[j][1], w, x.l) : x.l;
 #pragma unroll
@@ -632,7 +633,7 @@ __global__ __launch_bounds__(kMergeThreads) void decode_attn_merge(const AttnArg
   if (part == 0) {
     f32x4u o;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) o[k] = x.l > 0.f ? x.v[k] / x.l : 0.f;
+    for (int k = 0; k < 4; ++k) o[k] = x.l == 0.f ? 0.f : x.v[k] / x.l;
     *reinterpret_cast<f32x4u*>(a.out + (int64_t(r) * a.q_heads + h) * kDh + d) = o;
   }
 }

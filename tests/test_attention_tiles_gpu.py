@@ -205,3 +205,33 @@ def test_error_beside_a_float32_evaluation(dh, group):
     say(f"head_dim {dh}, group {group}: {kernel / np.linalg.norm(want):.2e} against 64 bits, "
         f"{kernel / ideal:.2f} times a float32 evaluation's")
     assert kernel <= 1.6 * ideal
+
+
+
+@pytest.mark.parametrize("dh,group", [(64, 2), (128, 4), (128, 8)])
+@pytest.mark.parametrize("split", [0, 64])
+@pytest.mark.parametrize("host", [False, True])
+def test_scores_that_are_nan_reach_the_output(dh, group, split, host):
+    """A NaN among a head's scores (a NaN in K or q, or a score of +inf, whose
+    weight is inf - inf) gives NaN, whether it stands beside finite scores or
+    fills a whole split; other heads and requests stay as they are."""
+    T = 150
+    q = torch.randn((1, group, dh), generator=torch.Generator("cuda").manual_seed(2),
+                    device="cuda").to(torch.bfloat16)
+    q[:, :, 3] = 1.0
+    pool, t = one_head_pool(T, dh, 56)
+    clean = attend(pool, q, T, 0.1, split, host)
+    assert np.isfinite(clean).all()
+    two = q.repeat(2, 1, 1)
+    two[1, group - 1, 0] = float("nan")
+    got = attend(pool, two, T, 0.1, split, host)
+    assert np.array_equal(got[0], clean[0])
+    assert np.array_equal(got[1, :-1], clean[0, :-1])
+    assert np.isnan(got[1, -1]).all()
+    for tokens, val in (((90,), np.nan), ((5,), np.inf), (range(64, 128), np.nan),
+                        ((149,), np.inf)):
+        pool, t = one_head_pool(T, dh, 56)
+        for x in tokens:
+            put(t, 0, x, 3, val)
+        got = attend(pool, q, T, 0.1, split, host)
+        assert np.isnan(got).all(), (tokens, val)
