@@ -35,6 +35,7 @@
 #include <mutex>
 
 #include "flowkv.h"
+#include "flowkv_device.h"
 #include "flowkv_status.h"
 
 using flowkv::fail;
@@ -57,6 +58,7 @@ typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 // wave, lost 2-50% at the same split: fewer workgroups to balance).
 constexpr int kWaves = 4;
 constexpr int kThreads = 64 * kWaves;
+constexpr int kTile = 32;                  // tokens per wave step
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLazy = 8.f;               // log2 of the largest unnormalised weight
 
@@ -149,6 +151,16 @@ __device__ __forceinline__ float hi_part(float x) {
   return __uint_as_float(__float_as_uint(x) & 0xffff0000u);
 }
 
+// The LDS of a pass-1 workgroup.
+template <int kDh>
+struct SplitLds {
+  int64_t off[FLOWKV_ATTN_MAX_SPLIT];      // byte offset of a token's row in the pool
+  // K's staging, a tile per wave; after the loop the waves' weighted sums
+  alignas(16) uint8_t area[kWaves * kTile * kDh * 2];
+  uint32_t dead[FLOWKV_ATTN_MAX_SPLIT / kTile];
+  float m[kWaves][16], l[kWaves][16];
+};
+
 // Pass 1 on the matrix cores.  Each wave takes its own tiles of 32 tokens,
 // four tiles apart; per tile:
 //   - K and V rows arrive whole: 16 lanes read one token's head vector (Dh 64:
@@ -200,13 +212,11 @@ __device__ __forceinline__ float hi_part(float x) {
 // output (a flag read at run time cost every other call 0.4 us).
 template <int kDh, int kG, bool kLM, bool kLens, bool kDirect>
 __device__ __forceinline__ void split_pass(const AttnArgs& a) {
-  constexpr int kTile = 32;                      // tokens per wave step
   constexpr int kI = kDh / 32;                   // MFMA steps of K.q
   constexpr int kT = kDh / 16;                   // dims a lane owns in P.V
   constexpr int kVW = kT / 2;                    // V words per token and lane
   constexpr int kPc = kDh / 8;                   // 16-byte pieces of a K row
   constexpr int kKL = kTile * kPc / 64;          // K loads of a tile and lane
-  constexpr int kTileBytes = kTile * kDh * 2;
   constexpr int kRep = kG == 8 ? 2 : 4;          // columns of S, and rows of P, per head
   using VT = typename Words<kVW>::T;
   const int g = blockIdx.x, split = blockIdx.y, r = blockIdx.z;
@@ -229,8 +239,7 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
   // outside the pool reads the pool's first slot and has its bit set in its
   // tile's mask.  The block IDs are fetched without waiting for the request's
   // length.
-  __shared__ __attribute__((aligned(16))) int64_t s_off[FLOWKV_ATTN_MAX_SPLIT];
-  __shared__ uint32_t s_dead[FLOWKV_ATTN_MAX_SPLIT / kTile];
+  __shared__ SplitLds<kDh> lds;
   constexpr int kStage = FLOWKV_ATTN_MAX_SPLIT / kThreads;
   int32_t blk[kStage], slot[kStage];
 #pragma unroll
@@ -283,17 +292,14 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
     const bool ok = x < n_tok && blk[i] >= 0 && blk[i] < a.pool_blocks;
     const uint64_t dead = __ballot(!ok);
     if (x < n_tiles * kTile) {
-      s_off[(x & -kTile) + (x & 3) * 8 + (x >> 2 & 7)] =
+      lds.off[(x & -kTile) + (x & 3) * 8 + (x >> 2 & 7)] =
           ok ? int64_t(uint64_t(uint32_t(blk[i])) * bstride + uint32_t(slot[i]) * sstride) : 0;
-      if (ln % kTile == 0) s_dead[x / kTile] = uint32_t(dead >> ln);
+      if (ln % kTile == 0) lds.dead[x / kTile] = uint32_t(dead >> ln);
     }
   }
 
-  // K's staging, a tile per wave; after the loop the area holds the waves'
-  // weighted sums
-  __shared__ __attribute__((aligned(16))) uint8_t s_area[kWaves * kTileBytes];
-  static_assert(sizeof(float) * kWaves * kG * kDh <= sizeof(s_area), "merge area fits");
-  u32x4* const s_k = reinterpret_cast<u32x4*>(s_area + wave * kTileBytes);
+  static_assert(sizeof(float) * kWaves * kG * kDh <= sizeof(lds.area), "merge area fits");
+  u32x4* const s_k = reinterpret_cast<u32x4*>(lds.area + wave * (kTile * kDh * 2));
 
   f32x4 o[kT];
 #pragma unroll
@@ -318,13 +324,13 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
 #pragma unroll
     for (int e = 0; e < kKL; ++e)
       kw[e] = Words<4>::load_nt(kbase + 16 * kp +
-                                s_off[real ? tile * kTile + k_at + e * (kStride / 4) : 0]);
+                                lds.off[real ? tile * kTile + k_at + e * (kStride / 4) : 0]);
   };
   auto load_v = [&](int tile, bool real) {
 #pragma unroll
     for (int e = 0; e < 8; ++e)
       vw[e] = Words<kVW>::load_nt(kbase + voff + c16 * (kVW * 4) +
-                                  s_off[real ? tile * kTile + 8 * q4 + e : 0]);
+                                  lds.off[real ? tile * kTile + 8 * q4 + e : 0]);
   };
   if (wave < n_tiles) {
     load_k(wave, true);
@@ -361,7 +367,7 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
     load_k(tile + kWaves, more);
     __builtin_amdgcn_sched_barrier(0);
     // bit 4 e: the lane's token 4 e + q4 of this tile is dead
-    uint32_t dead = __builtin_amdgcn_readfirstlane(s_dead[tile]);
+    uint32_t dead = __builtin_amdgcn_readfirstlane(lds.dead[tile]);
     const bool masked = dead != 0;               // uniform
     if (masked) {
       dead >>= q4;
@@ -459,15 +465,14 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
 
   // merge the waves: per head a weight exp2(m_wave - M); a wave that saw no
   // token has m = -inf and weighs nothing
-  __shared__ float s_m[kWaves][16], s_l[kWaves][16];
   lsum += __shfl_xor(lsum, 16);
   lsum += __shfl_xor(lsum, 32);
   if (q4 == 0) {
-    s_m[wave][c16] = mref;
-    s_l[wave][c16] = lsum;
+    lds.m[wave][c16] = mref;
+    lds.l[wave][c16] = lsum;
   }
   __syncthreads();  // every wave is past the loop: the area is free
-  float* const s_o = reinterpret_cast<float*>(s_area);   // [wave][head < kG][dim]
+  float* const s_o = reinterpret_cast<float*>(lds.area);   // [wave][head < kG][dim]
 #pragma unroll
   for (int j = 0; j < 4; j += kRep)              // a head's parts, smallest first
     if (const int h = (4 * q4 + j) / kRep; h < kG) {
@@ -492,13 +497,13 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
   float M = -INFINITY, L = 0.f;
   OutVec A = 0.f;
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) M = fmaxf(M, s_m[w][kRep * h]);
+  for (int w = 0; w < kWaves; ++w) M = fmaxf(M, lds.m[w][kRep * h]);
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) {
-    const float m = s_m[w][kRep * h];
+    const float m = lds.m[w][kRep * h];
     const float wt = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
     const OutLds x = *reinterpret_cast<const OutLds*>(&s_o[(w * kG + h) * kDh + d]);
-    L = fmaf(s_l[w][kRep * h], wt, L);
+    L = fmaf(lds.l[w][kRep * h], wt, L);
 #pragma unroll
     for (int k = 0; k < kOut; ++k) A[k] = fmaf(x[k], wt, A[k]);
   }
@@ -674,6 +679,22 @@ const void* pick_merge_waves(bool one) {
 const void* pick_merge(int D, bool lens, bool one) {
   if (D == 64) return lens ? pick_merge_waves<64, true>(one) : pick_merge_waves<64, false>(one);
   return lens ? pick_merge_waves<128, true>(one) : pick_merge_waves<128, false>(one);
+}
+
+// LDS that a launch of pass 1 asks for beyond the kernel's own, so that a CU
+// takes no third workgroup where two per CU hold them all (`live`: with the
+// lengths on the host the splits that do not leave at once, else all).  The
+// dispatcher fills a CU as far as registers and LDS allow before every CU has
+// its share: 342 workgroups of 24 requests on 2 KV heads took 26.4 us for 22.3,
+// 356 of 31 requests 47.0 for 38.1, 360 at 8 heads 18.1 for 15.5; of 50 other
+// calls of at most two per CU none was slower by more than the runs differ.
+// With a third allowed beyond that, a limit of one less than fit cost up to 14%.
+constexpr int64_t kCuLds = 160 * 1024;
+static_assert(sizeof(SplitLds<128>) <= kCuLds / 3, "two workgroups are spread by LDS alone");
+
+unsigned spread_lds(int D, int64_t live, int64_t cus) {
+  if (live > 2 * cus) return 0;
+  return unsigned(kCuLds / 3 + 1 - (D == 64 ? sizeof(SplitLds<64>) : sizeof(SplitLds<128>)));
 }
 
 int32_t auto_split(int32_t n_req, int32_t max_seq_len) {
@@ -903,24 +924,33 @@ int launch_attention(const flowkv_pool* pool, int32_t layer, const void* q_dev, 
   a.q_heads = q_heads;
   a.max_blocks = max_blocks;
   a.split_tokens = split_tokens;
-  a.max_splits = int32_t((int64_t(max_seq_len) + split_tokens - 1) / split_tokens);
+  a.max_splits = int32_t(splits);
   a.max_seq_len = max_seq_len;
   a.scale_log2 = scale * kLog2e;
   // a call whose longest request is one split needs no merge: pass 1 divides
   // and writes the output, which saves a launch (one request of 200 tokens
   // 7.5 against 5.0 us, 64 of 100 at 8 heads per KV head 13.2 against 9.4)
   const bool direct = a.max_splits == 1;
-  if (lens)
-    for (int32_t i = 0; i < n_req; ++i) a.lens[i] = seq_lens_host[i];
+  int64_t live = splits * n_req * kv_heads;
+  if (lens) {
+    live = 0;
+    for (int32_t i = 0; i < n_req; ++i) {
+      a.lens[i] = seq_lens_host[i];
+      const int64_t T = std::min(std::max(a.lens[i], 0), max_seq_len);
+      live += (T + split_tokens - 1) / split_tokens * kv_heads;
+    }
+  }
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   void* args[] = {&a};
   hipError_t e = hipSuccess;
   if (a.max_splits > 0) {
+    int cus = 0;
+    const int rc = flowkv::cu_count(&cus);
+    if (rc) return rc;
     SplitFn fn = pick_split(head_dim, G, lm, lens, direct);
     e = hipLaunchKernel(reinterpret_cast<const void*>(fn),
                         dim3(unsigned(kv_heads), unsigned(a.max_splits), unsigned(n_req)),
-                        dim3(kThreads),
-                        args, 0, st);
+                        dim3(kThreads), args, spread_lds(head_dim, live, cus), st);
   }
   if (e == hipSuccess && !direct) {
     // one wave per (query head, request) where its lane groups hold every

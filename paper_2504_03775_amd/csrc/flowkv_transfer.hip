@@ -37,6 +37,7 @@
 #include <cstdint>
 
 #include "flowkv.h"
+#include "flowkv_device.h"
 #include "flowkv_status.h"
 
 using flowkv::fail;
@@ -552,9 +553,11 @@ int default_threads(int64_t total_blocks, int64_t span) {
   return span <= kShortSpan ? kShortSpanThreads : kDefaultThreads;
 }
 
-std::atomic<int> g_cu_count[64];
+}  // namespace
 
-int cu_count(int* out) {
+static std::atomic<int> g_cu_count[64];
+
+int flowkv::cu_count(int* out) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return fail(FLOWKV_EHIP, "hipGetDevice: %s", hipGetErrorString(e));
@@ -573,6 +576,8 @@ int cu_count(int* out) {
   *out = c;
   return FLOWKV_OK;
 }
+
+namespace {
 
 struct Range {
   uintptr_t lo, hi;
@@ -744,7 +749,7 @@ int launch_transfer(const flowkv_pool* src, const flowkv_pool* dst,
   int64_t launch = a.units;
   if (grid == 0) {
     int cus = 0;
-    rc = cu_count(&cus);
+    rc = flowkv::cu_count(&cus);
     if (rc) return rc;
     launch = std::min<int64_t>(launch, int64_t(cus) * kMaxGridPerCU);
   } else {

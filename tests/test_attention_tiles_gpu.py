@@ -235,3 +235,18 @@ def test_scores_that_are_nan_reach_the_output(dh, group, split, host):
             put(t, 0, x, 3, val)
         got = attend(pool, q, T, 0.1, split, host)
         assert np.isnan(got).all(), (tokens, val)
+
+
+@pytest.mark.parametrize("dh,group", [(64, 2), (128, 8)])
+@pytest.mark.parametrize("past", [0, 1], ids=["two-per-cu", "one-more"])
+@pytest.mark.parametrize("host", [False, True])
+def test_workgroups_around_two_per_cu(dh, group, past, host):
+    """At most two workgroups per CU are launched with LDS added, so that no CU
+    takes a third; one more split and they are not.  Splits of one tile on two
+    KV heads; with the lengths on the host, beside requests that end early."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    geom = Geometry("spread", 1, 2, dh, 16, "bfloat16")
+    lens = [32 * (cus - 3) + past, 1, 32, 5] if host else [32 * cus + past]
+    say(f"spread: {lens}, {cus} CUs, host {host}")
+    run_case(geom, BM, sum(-(-t // 16) for t in lens) + 3, lens, 2 * group, 970 + past, 32,
+             host_lens=host)
