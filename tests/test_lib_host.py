@@ -790,3 +790,25 @@ def test_noalloc_attention_rejects_before_any_runtime_call():
     rc = attn_noalloc(p8, n_req=fits + 1, hq=32, hkv=8, max_seq=20000, split=1024)
     assert rc == fk.ECAP
     assert "scratch holds 16777216" in fk.lib().flowkv_last_error().decode()
+
+
+@pytest.mark.parametrize("private", [True, False])
+def test_current_stream_handle_with_and_without_the_private_call(monkeypatch, private):
+    """The binding reads the current stream's handle through a private call of
+    torch's, and through the public Stream object where torch lacks it; a
+    stream that the caller passes is taken as it is."""
+    import types
+
+    import torch
+
+    if private:
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda dev: 100 + dev,
+                            raising=False)
+        monkeypatch.setattr(torch.cuda, "current_stream", None)
+    else:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+        monkeypatch.setattr(torch.cuda, "current_stream",
+                            lambda: types.SimpleNamespace(cuda_stream=103))
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    assert fk._stream_handle(None) == 103
+    assert fk._stream_handle(types.SimpleNamespace(cuda_stream=7)) == 7
