@@ -3,10 +3,8 @@
 Every output element must lie within its own bound (tests/attn_tolerance.py):
 the float32 rounding of its scores, weights and sums, scaled by what the
 oracle returns beside the output -- sum_t p_t |V_t|, the spread
-sqrt(sum_t p_t^2 (V_t - o)^2) and the largest score magnitude -- plus, in the
-matrix-core pass (8 query heads per KV head, head_dim 128), the relative
-2^-16 of weights carried into P.V as two bfloat16 parts.  Each test prints
-its worst error and its worst ratio of error to bound.
+sqrt(sum_t p_t^2 (V_t - o)^2) and the largest score magnitude.  Each test
+prints its worst error and its worst ratio of error to bound.
 """
 
 import gc
@@ -79,8 +77,7 @@ def run_case(geom: Geometry, layout, pool_blocks, lens, q_heads, seed, split=0, 
     want, w1, w2, s1 = decode_attention_scales(host, bf16_to_f64(q), ctabs, eff, layer,
                                                geom.kv_heads, geom.head_dim, scale)
     err, ratio = attn_tolerance.check(
-        got, want, w1, w2, s1, eff, split or fk.flowkv_decode_attention_split(n, max_seq),
-        attn_tolerance.matrix_core_pass(q_heads, geom.kv_heads, geom.head_dim))
+        got, want, w1, w2, s1, eff, split or fk.flowkv_decode_attention_split(n, max_seq))
     say(f"  worst error / bound {ratio:.3f}")
     return got, err
 
@@ -168,7 +165,7 @@ def test_both_layouts_give_identical_outputs():
     assert torch.equal(outs[0], outs[1])
 
 
-HOST_LENS_SHAPES = [  # (layers, kv heads, head dim, block size, q heads): every pass
+HOST_LENS_SHAPES = [  # (layers, kv heads, head dim, block size, q heads): every group size
     (2, 2, 64, 16, 2), (2, 2, 64, 16, 4), (2, 1, 64, 16, 8), (2, 4, 128, 16, 4),
     (2, 2, 128, 16, 16), (2, 1, 128, 7, 1), (2, 2, 128, 16, 4),
 ]
@@ -180,10 +177,9 @@ def test_host_lengths_give_identical_outputs(layout, shape):
     """Lengths passed on the host travel in the kernel arguments: splits past
     a request's end then leave no record and the merge reads only the live
     ones.  The arithmetic is the same, so the outputs are bit-identical to the
-    device-lengths call, for every pass (vector at 1, 2, 4 and 8 query heads
-    per KV head, both head dims; matrix-core at 8 over head_dim 128), mixed
-    lengths with empty requests, lengths past max_seq_len and past the block
-    table; and they pass the oracle."""
+    device-lengths call, for 1, 2, 4 and 8 query heads per KV head and both
+    head dims, mixed lengths with empty requests, lengths past max_seq_len and
+    past the block table; and they pass the oracle."""
     L, hkv, dh, bs, hq = HOST_LENS_SHAPES[shape]
     geom = Geometry(f"hl{shape}", L, hkv, dh, bs, "bfloat16")
     g = np.random.default_rng(700 + shape)
@@ -224,7 +220,7 @@ def test_host_lengths_at_the_argument_capacity(n_req):
 
 
 @pytest.mark.parametrize("hq,hkv,dh", [(8, 1, 128), (4, 2, 64)],
-                         ids=["matrix-core-pass", "vector-pass"])
+                         ids=["8-heads-of-128", "2-heads-of-64"])
 def test_most_requests_one_token_each(hq, hkv, dh):
     """65,535 requests (the grid's limit) of one token each: a softmax over
     one token weighs it exactly 1, so every output is that token's V, bit
@@ -255,7 +251,7 @@ def test_most_requests_one_token_each(hq, hkv, dh):
 
 @pytest.mark.parametrize("host_lens", [False, True], ids=["lengths-on-device", "lengths-on-host"])
 @pytest.mark.parametrize("hq,hkv,dh", [(8, 1, 128), (4, 2, 64)],
-                         ids=["matrix-core-pass", "vector-pass"])
+                         ids=["8-heads-of-128", "2-heads-of-64"])
 def test_most_splits_constant_values(hq, hkv, dh, host_lens):
     """One 65,535-token request in one-token splits: 65,535 pass-1 workgroups
     per KV head (the grid's limit) and as many records for the merge.  With a
@@ -325,14 +321,13 @@ def test_length_caps_and_empty_request():
     assert np.all(z == 0)
 
 
-@pytest.mark.parametrize("hq", [8, 16], ids=["vector-pass", "matrix-core-pass"])
+@pytest.mark.parametrize("hq", [8, 16], ids=["4-per-kv-head", "8-per-kv-head"])
 @pytest.mark.parametrize("layout", [BM, LM], ids=lambda x: NAMES[x])
 def test_blocks_outside_the_pool_contribute_nothing(layout, hq):
     """A block ID outside the pool (negative or >= the pool's size) inside a
     request's length is skipped: the output equals attention over the tokens
     of the valid blocks alone (attention does not depend on token order).
-    8 query heads on 2 KV heads keep V in registers, 16 in LDS (a hole falls
-    inside a 32-token tile; split 64: two tiles)."""
+    A hole falls inside a 32-token tile; split 64: two tiles, by two waves."""
     geom = Geometry("holes", 3, 2, 128, 16, "bfloat16")
     B, layer, bs = 50, 1, 16
     pool = fk.KVPool(layout, make_device_pool(geom, layout, B, "cuda", 21))
@@ -371,23 +366,22 @@ def test_blocks_outside_the_pool_contribute_nothing(layout, hq):
         host, bf16_to_f64(q), [[lut[b] for b in t] for t in valid_tables], valid_lens, layer,
         geom.kv_heads, geom.head_dim, scale)
     # the kernel's chains run over the full lengths, holes included
-    err, ratio = attn_tolerance.check(got, want, w1, w2, s1, lens, 64,
-                                      attn_tolerance.matrix_core_pass(hq, 2, 128))
+    err, ratio = attn_tolerance.check(got, want, w1, w2, s1, lens, 64)
     say(f"holes {NAMES[layout]} hq={hq}: max error {err:.2e}, worst error / bound {ratio:.3f}")
 
 
 @pytest.mark.parametrize("layout", [BM, LM], ids=lambda x: NAMES[x])
 @pytest.mark.parametrize("split", [32, 64, 128, 160, 256, 384, 1024])
-def test_matrix_core_pass_tile_counts(layout, split):
-    """The matrix-core pass (8 query heads per KV head, head_dim 128) takes
-    32-token tiles, 4 waves a workgroup, and issues each tile's loads one tile
-    ahead into alternating buffers.  Lengths around tile and step edges
-    (1, 31..33, 127..129, 255, 257, 1000) under these split lengths give waves
-    0 to 8 tiles, odd and even counts, full and ragged last tiles."""
+def test_tile_counts_of_a_wave_over_split_lengths(layout, split):
+    """Pass 1 takes 32-token tiles, 4 waves a workgroup, and issues each tile's
+    loads a tile ahead (8 query heads per KV head, head_dim 128).  Lengths
+    around tile and step edges (1, 31..33, 127..129, 255, 257, 1000) under
+    these split lengths give waves 0 to 8 tiles, odd and even counts, full and
+    ragged last tiles."""
     geom = Geometry("tiles", 2, 2, 128, 16, "bfloat16")
     lens = [1, 31, 32, 33, 127, 128, 129, 255, 257, 1000]
     blocks = sum(-(-T // 16) for T in lens) + 8
-    say(f"matrix-core tiles {NAMES[layout]} split={split}")
+    say(f"tiles {NAMES[layout]} split={split}")
     _, err = run_case(geom, layout, blocks, lens, 16, 40 + split, split, layer=1)
     say(f"  max error {err:.2e}")
 
@@ -475,8 +469,7 @@ def test_bench_attention_workloads_full_size(name, layout):
     want, w1, w2, s1 = decode_attention_scales(host, bf16_to_f64(q[pick]), ctabs, picked, 0,
                                                geom.kv_heads, geom.head_dim, scale)
     err, ratio = attn_tolerance.check(
-        got[pick], want, w1, w2, s1, picked, fk.flowkv_decode_attention_split(n, max_seq),
-        attn_tolerance.matrix_core_pass(q_heads, geom.kv_heads, geom.head_dim))
+        got[pick], want, w1, w2, s1, picked, fk.flowkv_decode_attention_split(n, max_seq))
     say(f"  max error {err:.2e}, worst error / bound {ratio:.3f}")
     del pool
     torch.cuda.empty_cache()

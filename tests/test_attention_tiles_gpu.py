@@ -21,12 +21,12 @@ pytestmark = pytest.mark.gpu
                                                            (64, (1, 3, 15, 16, 17, 63, 64, 65)))
                                         for n in ns])
 def test_merge_at_its_record_counts(dh, records):
-    geom = Geometry("merge", 1, 2, dh, 16, "bfloat16")
     split = 16
     lens = [split * records, split * records - 5, max(1, split * records // 3)]
     say(f"merge: head_dim {dh}, {records} records")
-    # 3 query heads' worth of a wave's four, and whole fours
-    for hq in (2, 8):
+    # a workgroup of one wave a head takes four: half a four, one and a half, whole ones
+    for hq in (2, 6, 8):
+        geom = Geometry("merge", 1, 3 if hq == 6 else 2, dh, 16, "bfloat16")
         run_case(geom, (LM, BM)[records % 2], sum(-(-t // 16) for t in lens) + 3, lens, hq,
                  900 + records, split, host_lens=bool(hq == 8))
 

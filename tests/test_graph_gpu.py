@@ -30,7 +30,7 @@ def say(*a):
 
 
 @pytest.mark.parametrize("host_lens", [False, True], ids=["lengths-on-device", "lengths-on-host"])
-@pytest.mark.parametrize("hq", [8, 32], ids=["matrix-core-pass", "vector-pass"])
+@pytest.mark.parametrize("hq", [8, 32], ids=["8-heads-1-kv", "32-heads-8-kv"])
 def test_noalloc_attention_replays_in_a_graph(hq, host_lens):
     hkv = 1 if hq == 8 else 8
     geom = Geometry("graph-attn", 2, hkv, 128, 16, "bfloat16")

@@ -168,9 +168,9 @@ def test_rejects_bad_inputs():
 #
 # tests/attn_tolerance.py bounds |kernel - oracle| per output element from the
 # scales decode_attention_scales returns.  Here, in numpy, float32 evaluations
-# of attention stand in for kernels: two that are right (the vector pass's
-# arithmetic, and the matrix-core pass's weights carried as two bf16 parts)
-# must pass, and two with bugs a loose bound would let through must fail.
+# of attention stand in for kernels: two that are right (weights as float32, and
+# in the three bf16 parts that the kernels carry) must pass, and two with bugs a
+# loose bound would let through must fail.
 
 from tests import attn_tolerance  # noqa: E402
 
@@ -196,8 +196,8 @@ def long_request(T, hkv, hq, dh, seed):
 def float32_attention(kv, q, scale, hq, hkv, weights="f32", drop=None):
     """Attention of one request evaluated in float32: scores, exp2 weights
     against the largest score, their sum L, and sum_t w_t V_t / L with the
-    weights w_t taken as float32 ('f32'), as bf16(p) + bf16(p - bf16(p))
-    ('hi+lo'), or as bf16(p) alone ('hi').  `drop` leaves the 32 tokens from
+    weights w_t taken as float32 ('f32'), as three bf16 parts ('parts'), or as
+    bf16(p) alone ('hi').  `drop` leaves the 32 tokens from
     that index out of the weighted sum (a skipped tile)."""
     K, V = kv[0], kv[1]
     o = np.zeros((1, hq, K.shape[2]))
@@ -211,36 +211,36 @@ def float32_attention(kv, q, scale, hq, hkv, weights="f32", drop=None):
         hi = from_bf16(to_bf16(p)).astype(np.float32)
         if weights == "f32":
             num = p @ V[:, g, :]
-        elif weights == "hi":
-            num = hi @ V[:, g, :]
         else:
-            lo = from_bf16(to_bf16(p - hi)).astype(np.float32)
-            num = (hi @ V[:, g, :]).astype(np.float32) + (lo @ V[:, g, :]).astype(np.float32)
+            num, rest = hi @ V[:, g, :], p - hi
+            for _ in range({"hi": 0, "parts": 2}[weights]):
+                part = from_bf16(to_bf16(rest)).astype(np.float32)
+                num, rest = (num + part @ V[:, g, :]).astype(np.float32), rest - part
         o[0, h] = num.astype(np.float32) / L
     return o
 
 
-HQ, HKV, DH = 8, 1, 128     # the matrix-core pass's shape (one 70B TP=8 share)
+HQ, HKV, DH = 8, 1, 128     # one 70B TP=8 share
 
 
 @pytest.mark.parametrize("T", [50, 300, 4097, 20000])
 def test_tolerance_accepts_float32_evaluations(T):
     out, w1, w2, s1, kv, q, scale = long_request(T, HKV, HQ, DH, T)
-    for weights, mc in (("f32", False), ("hi+lo", True)):
+    for weights in ("f32", "parts"):
         got = float32_attention(kv, q, scale, HQ, HKV, weights)
-        attn_tolerance.check(got, out, w1, w2, s1, [T], 256, mc)
+        attn_tolerance.check(got, out, w1, w2, s1, [T], 256)
 
 
 @pytest.mark.parametrize("T", [300, 4097, 20000])
 def test_tolerance_rejects_weights_carried_as_bf16_alone(T):
-    """Dropping the low bf16 part of the matrix-core pass's weights (errors
-    near 1e-4 at these lengths) fails the bound."""
+    """Dropping the lower bf16 parts of the weights (errors near 1e-4 at these
+    lengths) fails the bound."""
     out, w1, w2, s1, kv, q, scale = long_request(T, HKV, HQ, DH, T)
     got = float32_attention(kv, q, scale, HQ, HKV, "hi")
-    tol = attn_tolerance.tolerance(w1, w2, s1, [T], 256, True)
+    tol = attn_tolerance.tolerance(w1, w2, s1, [T], 256)
     assert np.any(np.abs(got - out) > tol)
     with pytest.raises(AssertionError):
-        attn_tolerance.check(got, out, w1, w2, s1, [T], 256, True)
+        attn_tolerance.check(got, out, w1, w2, s1, [T], 256)
 
 
 def test_tolerance_rejects_a_skipped_tile_in_every_head():
@@ -248,8 +248,8 @@ def test_tolerance_rejects_a_skipped_tile_in_every_head():
     fails the bound in every query head."""
     T = 32000
     out, w1, w2, s1, kv, q, scale = long_request(T, HKV, HQ, DH, 7)
-    got = float32_attention(kv, q, scale, HQ, HKV, "hi+lo", drop=16000)
-    tol = attn_tolerance.tolerance(w1, w2, s1, [T], 1024, True)
+    got = float32_attention(kv, q, scale, HQ, HKV, "parts", drop=16000)
+    tol = attn_tolerance.tolerance(w1, w2, s1, [T], 1024)
     bad = np.abs(got - out) > tol
     assert bad.any(axis=2).all(), bad.any(axis=2)
 

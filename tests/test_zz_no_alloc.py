@@ -62,11 +62,11 @@ def both(geom, args, scale, layer):
 
 
 CASES = {
-    # vector pass: 32 query heads on 8 KV heads (Llama-3-8B), block-major
-    "vector-pass": (Geometry("8b", 4, 8, 128, 16, "bfloat16"), BM, 32,
+    # 32 query heads on 8 KV heads (Llama-3-8B), block-major
+    "32-heads-8-kv": (Geometry("8b", 4, 8, 128, 16, "bfloat16"), BM, 32,
                     [[5000, 1, 2345, 777], [700]]),
-    # matrix-core pass: 8 query heads on 1 KV head (the 70B TP=8 share), layer-major
-    "matrix-core-pass": (Geometry("70b", 3, 1, 128, 16, "bfloat16"), LM, 8,
+    # 8 query heads on 1 KV head (the 70B TP=8 share), layer-major
+    "8-heads-1-kv": (Geometry("70b", 3, 1, 128, 16, "bfloat16"), LM, 8,
                          [[3000, 40, 4097], [100]]),
     # head_dim 64, two query heads per KV head, odd block size
     "head-dim-64": (Geometry("d64", 2, 4, 64, 7, "bfloat16"), BM, 8, [[1500, 333], [65]]),
