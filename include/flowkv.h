@@ -353,9 +353,12 @@ int flowkv_decode_attention_workspace(int32_t n_req, int32_t q_heads, int32_t he
    caller, busy until the stream passes the call (NULL when that is 0).  Tokens beyond
    max_blocks x block_size or beyond max_seq_len are not read; a block ID
    outside the pool contributes nothing; a request with no tokens gets zeros.
+   A score that is NaN or +inf makes its head's output NaN; one of -inf weighs
+   nothing.
    head_dim 64 or 128; q_heads / kv_heads in {1, 2, 4, 8}; split_tokens 0 =
    the default rule (flowkv_decode_attention_split), else
-   1..FLOWKV_ATTN_MAX_SPLIT.  Two launches on hip_stream.  At most 65,535
+   1..FLOWKV_ATTN_MAX_SPLIT.  Two launches on
+   hip_stream, one where max_seq_len fits a single split.  At most 65,535
    requests and 65,535 splits (ceil(max_seq_len / split_tokens)) per call,
    and max_blocks x block_size at most 2^31 - 1 tokens.
    EINVAL for bad shapes or pointers, ECAP for a short workspace. */

@@ -201,7 +201,7 @@ struct SplitLds {
 // of the time its 16 KB take at 6 TB/s, whatever G is, so one form serves 1 to
 // 8 query heads per KV head.  A CU alone draws about 40 bytes a nanosecond, with
 // four waves or eight.  Registers (166 a lane at Dh 128) allow three workgroups
-// per CU, at Dh 64 (96-98) four are asked for.  Both passes, against the form
+// per CU, at Dh 64 (94-96) four are asked for.  Both passes, against the form
 // before this one (vector units up to 4 heads per KV head and at head_dim 64;
 // events around graphs, one MI355X): 32 requests of 2,000-20,000 tokens, G 4,
 // 255.9 us for 258.9; 48 of 30-1,500, 37.9 for 52.5; one of 13,000, 14.5 for
@@ -520,7 +520,7 @@ __device__ __forceinline__ void split_pass(const AttnArgs& a) {
 
 // (As the kernel's own body, split_pass came out 6% longer, and a 200-token
 // call took 5.4 us for 5.2.)
-// The waves per SIMD are an upper bound too: at Dh 64 the 96 registers would
+// The waves per SIMD are an upper bound too: at Dh 64 the registers would
 // let a fifth workgroup onto a CU while others are idle (24 requests of
 // 300-6,000 tokens 25.8 us for 22.7).
 template <int kDh, int kG, bool kLM, bool kLens, bool kDirect>

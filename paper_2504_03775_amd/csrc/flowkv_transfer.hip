@@ -537,12 +537,16 @@ constexpr int64_t kMaxGridPerCU = 2048;
 //   threads (8 KiB tiles).  One MI355X, 20 launches in a graph, 1024 against
 //   128 threads: 256 KiB 3.9 against 3.1 us, one layer of 60 blocks (3.8 MiB)
 //   5.3 against 4.4, of 125 (7.8 MiB) 6.3 against 5.6; of 250 (15.6 MiB) the
-//   other way, 8.7 against 9.1.
+//   other way, 8.7 against 9.1.  On data that no cache holds: 11-36% ahead up
+//   to 8 MiB, 4-10% at 9-10 MiB, 3-7% behind at 14-16 MiB of 64 KiB blocks; the
+//   line lies on the near side of where they cross.
 // - Above, where a block's span fills one line of 1024 threads at most (16
 //   KiB), such a workgroup had one vector per lane: 256 threads carry the span
 //   with four.  1,024 blocks of 16 KiB 10.9 against 8.2 us, 2,000 of 14 KiB
-//   18.4 against 12.4.  From 56 KiB to a full tile 1024 threads are within 4%
-//   either way on 16-130 MiB, and 10% ahead on 260 MiB and more.
+//   18.4 against 12.4; on data that no cache holds, 12 to 512 MiB in every
+//   layout pair, blocks of 16 KiB 14-24% ahead, of 8 KiB 49-100%.  From 56 KiB to
+//   a full tile 1024 threads are within 4% either way on 16-130 MiB, and 10%
+//   ahead on 260 MiB and more.
 constexpr int64_t kSmallBytes = int64_t(8) << 20;
 constexpr int kSmallThreads = 128;
 constexpr int64_t kShortSpan = int64_t(kDefaultThreads) * 16;
