@@ -689,11 +689,14 @@ const void* pick_merge(int D, bool lens, bool one) {
 // 356 of 31 requests 47.0 for 38.1, 360 at 8 heads 18.1 for 15.5; of 50 other
 // calls of at most two per CU none was slower by more than the runs differ.
 // With a third allowed beyond that, a limit of one less than fit cost up to 14%.
+// No more workgroups than the smallest partition of the card has CUs are left as
+// they are, without a lookup of the CU count (0.1 us of a call).
+constexpr int64_t kFewestCus = 32;
 constexpr int64_t kCuLds = 160 * 1024;
 static_assert(sizeof(SplitLds<128>) <= kCuLds / 3, "two workgroups are spread by LDS alone");
 
 unsigned spread_lds(int D, int64_t live, int64_t cus) {
-  if (live > 2 * cus) return 0;
+  if (live <= kFewestCus || live > 2 * cus) return 0;
   return unsigned(kCuLds / 3 + 1 - (D == 64 ? sizeof(SplitLds<64>) : sizeof(SplitLds<128>)));
 }
 
@@ -945,8 +948,10 @@ int launch_attention(const flowkv_pool* pool, int32_t layer, const void* q_dev, 
   hipError_t e = hipSuccess;
   if (a.max_splits > 0) {
     int cus = 0;
-    const int rc = flowkv::cu_count(&cus);
-    if (rc) return rc;
+    if (live > kFewestCus) {
+      const int rc = flowkv::cu_count(&cus);
+      if (rc) return rc;
+    }
     SplitFn fn = pick_split(head_dim, G, lm, lens, direct);
     e = hipLaunchKernel(reinterpret_cast<const void*>(fn),
                         dim3(unsigned(kv_heads), unsigned(a.max_splits), unsigned(n_req)),
