@@ -51,8 +51,9 @@ def test_attention_kernels_use_no_scratch_and_keep_their_occupancy(asm):
     the merge one per head_dim, source of the lengths and width.  None uses
     scratch memory or spills, and pass 1's registers (512 a SIMD lane, taken
     in eights) allow three workgroups of four waves per CU at head_dim 128 and
-    four at 64."""
-    split, merge = kernel_entries(asm, "decode_attn_split"), kernel_entries(asm, "decode_attn_merge")
+    four at 64, and no more."""
+    split = kernel_entries(asm, "decode_attn_split")
+    merge = kernel_entries(asm, "decode_attn_merge")
     assert len(split) == 2 * 4 * 2 * 2 * 2, sorted(split)
     assert len(merge) == 2 * 2 * 2, sorted(merge)
     for n, e in {**split, **merge}.items():
@@ -67,6 +68,11 @@ def test_attention_kernels_use_no_scratch_and_keep_their_occupancy(asm):
         lds = int(re.search(r"\.group_segment_fixed_size:\s+(\d+)", e).group(1))
         assert waves * (-(-vgprs // 8) * 8) <= 512, (n, vgprs)
         assert waves * lds <= 160 * 1024, (n, lds)
+        # what the launch allocates: at head_dim 64 a fifth workgroup must not fit
+        m = re.search(rf"\.amdhsa_kernel {re.escape(n)}\n.*?\.amdhsa_next_free_vgpr (\d+)",
+                      asm, re.S)
+        taken = -(-int(m.group(1)) // 8) * 8
+        assert waves * taken <= 512 < (waves + 1) * taken, (n, taken)
 
 
 # ---- the transfer kernels: no scratch memory, no spills ------------------------
